@@ -483,12 +483,12 @@ def measure(cfg, steps, warmup, u_steps, u_warmup, torch, capi, actor, record=Fa
     return r, live
 
 
-KERNEL_NAMES = {"gemm_nt": "gemm_mfma_kernel<true, true>",
-                "gemm_nn": "gemm_mfma_kernel<true, false>",
-                "gemm_tn": "gemm_mfma_kernel<false, false>",
-                "gemm4_nt": "gemm_mfma4s_kernel<true, true>",
-                "gemm4_nn": "gemm_mfma4s_kernel<true, false>",
-                "gemm4_tn": "gemm_mfma4s_kernel<false, false>", "attn_fwd": "attn_fwd_mfma_kernel",
+KERNEL_NAMES = {"gemm_nt": "gemm_mfma_kernel<Cfg8, true, true>",
+                "gemm_nn": "gemm_mfma_kernel<Cfg8, true, false>",
+                "gemm_tn": "gemm_mfma_kernel<Cfg8, false, false>",
+                "gemm4_nt": "gemm_mfma_kernel<Cfg4, true, true>",
+                "gemm4_nn": "gemm_mfma_kernel<Cfg4, true, false>",
+                "gemm4_tn": "gemm_mfma_kernel<Cfg4, false, false>", "attn_fwd": "attn_fwd_mfma_kernel",
                 "lm_fwd": "lm_fwd_fused_kernel", "lm_dz": "lm_dz_fused_kernel"}
 
 

@@ -1,7 +1,7 @@
 // GEMMs of the block and the LM head.
 //
-// bfloat16: v_mfma_f32_32x32x16_bf16 tiles, float32 accumulation, LDS
-// double-buffered, 256x256x64 workgroup tiles on 8 waves (128x64 per wave).
+// bfloat16: v_mfma_f32_16x16x32_bf16 tiles, float32 accumulation, 256x256
+// workgroup tiles on 8 waves (128x64 per wave) or 4 (128x128).
 // Operands are copied into LDS in their memory order: a K-major one as
 // [row][k], an M/N-major one (the weight-gradient GEMMs read activations
 // [tokens, features]) as [k][row], whose MFMA fragments come out of LDS
@@ -33,20 +33,8 @@ AJ_DEV void swiglu_grad(float ds, float g, float u, float &dg, float &du) {
   du = ds * g * sg;
 }
 
-using gemm_core::f32x16_t;
-
-// LDS stages of the staged GEMM kernels (128 KB).  A fifth stage (the whole
-// 160 KB, copies four k-steps ahead) measured no faster: the copies are bound
-// by the rate of 64-byte row requests, not by how far ahead they run.
-constexpr int kStages = 4;
-
-// A second reduction segment with the operand layouts of the first:
-// C = A B + A2 B2 over k in [0, K) and [0, K2).
-struct Seg2 {
-  const bf16_t *A; int64_t lda;
-  const bf16_t *B; int64_t ldb;
-  int K;
-};
+using gemm_core::f32x4_t;
+using gemm_core::Seg;
 
 // Output modes of the epilogue's fast path (interior tiles, aligned rows).
 enum { kEpPartial, kEpAccum, kEpF32, kEpF32R, kEpBf16, kEpBf16R, kEpSwiglu };
@@ -58,7 +46,7 @@ template <int MODE, typename Cfg>
 AJ_DEV void store_pass(const float *stage, int i, int m0, int n0, int64_t ldo, float *P,
                        const EpArgs &ep) {
   static_assert(Cfg::WTM == 128 && Cfg::BN == 256, "two wave rows of 128, 256 columns");
-  constexpr int LDW = Cfg::BN + 8;
+  constexpr int LDW = Cfg::BN + 4;
   constexpr int Q = 64 * 64 / Cfg::NT;
   float4 v[Q];
 #pragma unroll
@@ -140,46 +128,33 @@ AJ_DEV void epi_barrier() {
   gemm_core::bar_nofence();
 }
 
-// Shared body of the two GEMM kernels: main loop of configuration C (and the
+// Shared body of the GEMM kernels: main loop of configuration Cfg (and the
 // second segment's, SEG2), then the epilogue through LDS.
-template <bool A_K, bool B_K, typename Cfg, bool SEG2 = false, bool STAGED = false,
-          typename SM = gemm_core::Smem<A_K, B_K, Cfg>>
+template <bool A_K, bool B_K, typename Cfg, bool SEG2 = false>
 AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int64_t lda,
-                      const bf16_t *B, int64_t ldb, const EpArgs &ep, float *partial, SM &sm,
-                      const Seg2 &s2 = Seg2{}) {
+                      const bf16_t *B, int64_t ldb, const EpArgs &ep, float *partial,
+                      gemm_core::Smem<Cfg, A_K, B_K> &sm, const Seg &s2 = Seg{}) {
   const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
   const gemm_core::TileIdx ti = gemm_core::tile_of(blockIdx.x, gridDim.x, tiles_m, tiles_n);
   const int m0 = ti.tm * Cfg::BM, n0 = ti.tn * Cfg::BN;
   const int kbeg = blockIdx.z * k_per_split;
   const int kend = min(K, kbeg + k_per_split);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = gemm_core::wave_id();
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-  f32x16_t acc[Cfg::TM][Cfg::TN];
-  if constexpr (STAGED && Cfg::NT == 256) {
-    static_assert(!SEG2, "the staged loops take one segment");
-    gemm_core::mainloop4s<A_K, B_K, SM::kStages>(acc, A, lda, B, ldb, M, N, m0, n0, kbeg, kend,
-                                                 sm);
-  } else if constexpr (STAGED) {
-    static_assert(!SEG2, "the staged loops take one segment");
-    gemm_core::mainloop8s<A_K, B_K, Cfg, SM::kStages>(acc, A, lda, B, ldb, M, N, m0, n0, kbeg,
-                                                      kend, sm);
-  } else {
-    static_assert(Cfg::NT == 512, "8-wave tile");
-    gemm_core::mainloop<A_K, B_K, Cfg>(acc, A, lda, B, ldb, M, N, m0, n0, kbeg, kend, sm);
-    if constexpr (SEG2)
-      gemm_core::mainloop<A_K, B_K, Cfg>(acc, s2.A, s2.lda, s2.B, s2.ldb, M, N, m0, n0, 0, s2.K,
-                                         sm, false);
-  }
+  f32x4_t acc[Cfg::TM][Cfg::TN];
+  gemm_core::mainloop<Cfg, A_K, B_K, SEG2>(acc, Seg{A, lda, B, ldb, kbeg, kend}, M, N, m0, n0, sm,
+                                           s2);
   epi_barrier();
 
-  // Epilogue through LDS, 32 rows of each wave row at a time: the lane's
-  // accumulators (column lane%32, rows 8*(r/4) + 4*(lane/32) + r%4 of each
-  // 32x32 tile) are staged as rows, then written out 4 columns per lane.
+  // Epilogue through LDS, 32 rows of each wave row (two accumulator rows of
+  // tiles) at a time: a lane's four consecutive columns of a row go out as one
+  // 16-byte write, then rows are stored 4 columns per lane.  The padding of 4
+  // floats per row puts the 16 rows of a write on different banks.
   // Interior tiles with aligned rows take a pass specialised to the output
   // mode (no per-element branches, the pass's LDS reads issued together);
   // edge tiles go element by element.
   float *stage = reinterpret_cast<float *>(&sm);
-  constexpr int LDW = Cfg::BN + 8;
+  constexpr int LDW = Cfg::BN + 4;
   float *P = partial ? partial + (int64_t)blockIdx.z * M * N : nullptr;
   const int64_t ldo = partial ? N : ep.ldc;
   const bool fast = ep.vec && m0 + Cfg::BM <= M && n0 + Cfg::BN <= N;
@@ -189,14 +164,13 @@ AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int
                    : ep.c_f32 ? (ep.R ? kEpF32R : kEpF32)
                               : (ep.R ? kEpBf16R : kEpBf16);
 #pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i) {
+  for (int i = 0; i < Cfg::TM / 2; ++i) {
 #pragma unroll
-    for (int j = 0; j < Cfg::TN; ++j)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int lr = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-        stage[lr * LDW + wn * Cfg::WTN + j * 32 + (lane & 31)] = acc[i][j][r];
-      }
+      for (int j = 0; j < Cfg::TN; ++j)
+        *reinterpret_cast<f32x4_t *>(stage + (wm * 32 + 16 * h + (lane & 15)) * LDW +
+                                     gemm_core::acc_col<Cfg>(wn, j, lane)) = acc[2 * i + h][j];
     epi_barrier();
     if (fast) {
       switch (mode) {
@@ -283,35 +257,23 @@ AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int
   }
 }
 
-// 8 waves of 128x64: the default.
-template <bool A_K, bool B_K>
-__global__ __launch_bounds__(gemm_core::Cfg::NT, 1) void gemm_mfma_kernel(
+// Cfg8 is the default, Cfg4 takes reductions of kLongK and more.
+template <typename Cfg, bool A_K, bool B_K>
+__global__ __launch_bounds__(Cfg::NT, 1) void gemm_mfma_kernel(
     int M, int N, int K, int k_per_split, const bf16_t *A, int64_t lda, const bf16_t *B,
     int64_t ldb, EpArgs ep, float *partial) {
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem4s<A_K, B_K, kStages> sm;
-  gemm_tile<A_K, B_K, gemm_core::Cfg, false, true>(M, N, K, k_per_split, A, lda, B, ldb, ep,
-                                                   partial, sm);
+  __shared__ __attribute__((aligned(16))) gemm_core::Smem<Cfg, A_K, B_K> sm;
+  gemm_tile<A_K, B_K, Cfg>(M, N, K, k_per_split, A, lda, B, ldb, ep, partial, sm);
 }
 
-// 4 waves of 128x128 with 32-wide k-steps in four LDS stages (copies three
-// k-steps ahead): reductions of kLongK and more.
+// The 8-wave kernel with a second reduction segment with the operand layouts of
+// the first, C = A B + A2 B2 (no split-K; used with either reduction length).
 template <bool A_K, bool B_K>
-__global__ __launch_bounds__(gemm_core::Cfg4::NT, 1) void gemm_mfma4s_kernel(
-    int M, int N, int K, int k_per_split, const bf16_t *A, int64_t lda, const bf16_t *B,
-    int64_t ldb, EpArgs ep, float *partial) {
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem4s<A_K, B_K, kStages> sm;
-  gemm_tile<A_K, B_K, gemm_core::Cfg4, false, true>(M, N, K, k_per_split, A, lda, B, ldb, ep,
-                                                    partial, sm);
-}
-
-// The 8-wave kernel with a second reduction segment (no split-K; used with
-// either reduction length).
-template <bool A_K, bool B_K>
-__global__ __launch_bounds__(gemm_core::Cfg::NT, 1) void gemm_mfma_seg2_kernel(
-    int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B, int64_t ldb, Seg2 s2,
+__global__ __launch_bounds__(gemm_core::Cfg8::NT, 1) void gemm_mfma_seg2_kernel(
+    int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B, int64_t ldb, Seg s2,
     EpArgs ep) {
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem<A_K, B_K, gemm_core::Cfg> sm;
-  gemm_tile<A_K, B_K, gemm_core::Cfg, true>(M, N, K, K, A, lda, B, ldb, ep, nullptr, sm, s2);
+  __shared__ __attribute__((aligned(16))) gemm_core::Smem<gemm_core::Cfg8, A_K, B_K> sm;
+  gemm_tile<A_K, B_K, gemm_core::Cfg8, true>(M, N, K, K, A, lda, B, ldb, ep, nullptr, sm, s2);
 }
 
 constexpr int kLongK = 4096;
@@ -394,16 +356,16 @@ void launch_mfma(const Gemm &g, const EpArgs &ep, int kps, bool long_k, hipStrea
   dim3 grid(tiles, 1, g.split_k);
   float *part = g.split_k > 1 ? g.partial : nullptr;
   if (g.K2 > 0) {
-    const Seg2 s2{(const bf16_t *)g.A2, g.lda2, (const bf16_t *)g.B2, g.ldb2, g.K2};
-    gemm_mfma_seg2_kernel<A_K, B_K><<<tiles, gemm_core::Cfg::NT, 0, s>>>(
+    const Seg s2{(const bf16_t *)g.A2, g.lda2, (const bf16_t *)g.B2, g.ldb2, 0, g.K2};
+    gemm_mfma_seg2_kernel<A_K, B_K><<<tiles, gemm_core::Cfg8::NT, 0, s>>>(
         g.M, g.N, g.K, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, s2, ep);
     return;
   }
   if (long_k)
-    gemm_mfma4s_kernel<A_K, B_K><<<grid, gemm_core::Cfg4::NT, 0, s>>>(
+    gemm_mfma_kernel<gemm_core::Cfg4, A_K, B_K><<<grid, gemm_core::Cfg4::NT, 0, s>>>(
         g.M, g.N, g.K, kps, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, ep, part);
   else
-    gemm_mfma_kernel<A_K, B_K><<<grid, gemm_core::Cfg::NT, 0, s>>>(
+    gemm_mfma_kernel<gemm_core::Cfg8, A_K, B_K><<<grid, gemm_core::Cfg8::NT, 0, s>>>(
         g.M, g.N, g.K, kps, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, ep, part);
 }
 

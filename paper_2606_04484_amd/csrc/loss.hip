@@ -288,35 +288,13 @@ __global__ __launch_bounds__(256) void dz_kernel(const float *z, int n, int cw, 
 // ---------------------------------------------------------------- fused (bfloat16)
 namespace gemm_core = aj::gemm_core;
 using Cfg = gemm_core::CfgWide;
-template <bool A_K, bool B_K> using Smem = gemm_core::Smem4s<A_K, B_K>;
-using gemm_core::f32x16_t;
+template <bool B_K> using Smem = gemm_core::Smem<Cfg, true, B_K>;
+using gemm_core::f32x4_t;
 constexpr float kLog2e = 1.4426950408889634f;
 // 2^x on the hardware unit (v_exp_f32) for arguments <= 0 or -inf (a
 // logit minus a running maximum or the log-sum-exp): no range handling needed.
 AJ_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr float kLn2 = 0.6931471805599453f;
-
-// Reductions over each row of 16 lanes on the DPP network (no LDS traffic):
-// swaps within pairs and quads, then the mirrors of 8 and 16 lanes.  Every
-// lane of the row ends with the result.
-template <int CTRL>
-AJ_DEV float dpp(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               0xF, 0xF, false));
-}
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E, kRowHalfMirror = 0x141, kRowMirror = 0x140;
-AJ_DEV float row16_max(float v) {
-  v = fmaxf(v, dpp<kQuadXor1>(v));
-  v = fmaxf(v, dpp<kQuadXor2>(v));
-  v = fmaxf(v, dpp<kRowHalfMirror>(v));
-  return fmaxf(v, dpp<kRowMirror>(v));
-}
-AJ_DEV float row16_sum(float v) {
-  v += dpp<kQuadXor1>(v);
-  v += dpp<kQuadXor2>(v);
-  v += dpp<kRowHalfMirror>(v);
-  return v + dpp<kRowMirror>(v);
-}
 
 // LDS writes (or reads) complete, then a barrier; unlike __syncthreads this
 // does not wait for the workgroup's global stores.
@@ -333,7 +311,7 @@ template <bool B_K>
 __global__ __launch_bounds__(Cfg::NT, 1) void lm_fwd_fused_kernel(
     int n, int V, int d, const bf16_t *hn, const bf16_t *wv, int ldw, const int32_t *tpos,
     const int32_t *tok, float2 *tile_ms, float *zt, float *zkeep) {
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem4s<true, B_K, 4> sm;
+  __shared__ __attribute__((aligned(16))) Smem<B_K> sm;
   __shared__ int ttok[Cfg::BM];
   __shared__ float2 red[Cfg::WN][Cfg::BM];
   const int tiles_m = (n + Cfg::BM - 1) / Cfg::BM, tiles_n = (V + Cfg::BN - 1) / Cfg::BN;
@@ -343,67 +321,79 @@ __global__ __launch_bounds__(Cfg::NT, 1) void lm_fwd_fused_kernel(
     const int m = m0 + threadIdx.x;
     ttok[threadIdx.x] = m < n ? tok[tpos[m]] : -1;
   }
-  f32x16_t acc[Cfg::TM][Cfg::TN];
-  gemm_core::mainloop8s<true, B_K, Cfg, 4>(acc, hn, d, wv, ldw, n, V, m0, n0, 0, d, sm);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  f32x4_t acc[Cfg::TM][Cfg::TN];
+  gemm_core::mainloop<Cfg, true, B_K>(acc, gemm_core::Seg{hn, d, wv, ldw, 0, d}, n, V, m0, n0, sm);
+  const int lane = threadIdx.x & 63, wave = gemm_core::wave_id();
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-  // A row of this wave's 128 columns lives in the 32 lanes of a half-wave, 4
-  // columns each: reduce over 16 lanes by DPP, then across the two rows of
-  // 16 with one exchange per row, issued for all 16 rows of a pass together.
-  const int col0 = n0 + wn * Cfg::WTN + (lane & 31);
+  // A row of this wave's 128 columns lives in 4 lanes (16 apart), 32 columns
+  // each: reduce in the lane, then across the four with two exchanges.
+  const int col0 = n0 + gemm_core::acc_col<Cfg>(wn, 0, lane);   // columns col0 + 16 j + r
   if (zkeep) {
-    // the tile's logits for the backward: per accumulator row, the 32 lanes
-    // of a half-wave store 32 consecutive columns
+    // the tile's logits for the backward, four consecutive columns at a time
+    const bool vec = V % 4 == 0;
 #pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
+    for (int i = 0; i < Cfg::TM; ++i) {
+      const int m = m0 + gemm_core::acc_row<Cfg>(wm, i, lane);
+      if (m >= n) continue;
+      float *zr = zkeep + (int64_t)m * V;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + gemm_core::acc_row<Cfg>(wm, i, r, lane);
-        if (m >= n) continue;
-        float *zr = zkeep + (int64_t)m * V;
+      for (int j = 0; j < Cfg::TN; ++j) {
+        const int c = col0 + 16 * j;
+        if (vec) {
+          if (c < V) *reinterpret_cast<f32x4_t *>(zr + c) = acc[i][j];
+        } else {
 #pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-          if (col0 + 32 * j < V) zr[col0 + 32 * j] = acc[i][j][r];
+          for (int r = 0; r < 4; ++r)
+            if (c + r < V) zr[c + r] = acc[i][j][r];
+        }
       }
+    }
   }
   auto epilogue = [&](auto inside) {
     constexpr bool kInside = decltype(inside)::value;   // every column < V
+    float mx[Cfg::TM], sm_[Cfg::TM];
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i) {
-      float mx[16], sm_[16];
+      float m = -INFINITY;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float m = -INFINITY;
+      for (int j = 0; j < Cfg::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kInside || col0 + 16 * j + r < V) m = fmaxf(m, acc[i][j][r]);
+      mx[i] = m * kLog2e;
+    }
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) mx[i] = fmaxf(mx[i], __shfl_xor(mx[i], 16, 64));
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) mx[i] = fmaxf(mx[i], __shfl_xor(mx[i], 32, 64));
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) {
+      float t = 0.f;
+#pragma unroll
+      for (int j = 0; j < Cfg::TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kInside || col0 + 16 * j + r < V) t += fast_exp2(acc[i][j][r] * kLog2e - mx[i]);
+      sm_[i] = t;
+    }
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) sm_[i] += __shfl_xor(sm_[i], 16, 64);
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) sm_[i] += __shfl_xor(sm_[i], 32, 64);
+#pragma unroll
+    for (int i = 0; i < Cfg::TM; ++i) {
+      const int rl = gemm_core::acc_row<Cfg>(wm, i, lane);
+      if (lane < 16) red[wn][rl] = make_float2(mx[i], sm_[i]);
+      // the target's logit, in the lane that holds its column
+      const int t = ttok[rl] - col0;
+      if (t >= 0 && t < Cfg::TN * 16 && (t & 15) < 4 && m0 + rl < n) {
+        float z = acc[i][0][0];
 #pragma unroll
         for (int j = 0; j < Cfg::TN; ++j)
-          if (kInside || col0 + 32 * j < V) m = fmaxf(m, acc[i][j][r]);
-        mx[r] = row16_max(m * kLog2e);
-      }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) mx[r] = fmaxf(mx[r], __shfl_xor(mx[r], 16, 64));
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float t = 0.f;
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-          if (kInside || col0 + 32 * j < V) t += fast_exp2(acc[i][j][r] * kLog2e - mx[r]);
-        sm_[r] = row16_sum(t);
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sm_[r] += __shfl_xor(sm_[r], 16, 64);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = gemm_core::acc_row<Cfg>(wm, i, r, lane);
-        if ((lane & 31) == 0) red[wn][rl] = make_float2(mx[r], sm_[r]);
-        // the target's logit, in the lane that holds its column
-        const int t = ttok[rl] - col0;
-        if (t >= 0 && t < Cfg::TN * 32 && (t & 31) == 0 && m0 + rl < n) {
-          float z = acc[i][0][r];
-#pragma unroll
-          for (int j = 1; j < Cfg::TN; ++j)
-            if (t == 32 * j) z = acc[i][j][r];
-          zt[m0 + rl] = z;
-        }
+          for (int r = 0; r < 4; ++r)
+            if (t == 16 * j + r) z = acc[i][j][r];
+        zt[m0 + rl] = z;
       }
     }
   };
@@ -493,10 +483,7 @@ __global__ __launch_bounds__(Cfg::NT, 1) void lm_dz_fused_kernel(
     int n, int cw, int c0, int d, const bf16_t *hn, const bf16_t *wc, int ldw,
     const int32_t *tpos, const int32_t *tok, const float *lse, const float *g, bf16_t *dz,
     int ldz) {
-  // The body is device code only: this compiler's host pass rejects the
-  // main-loop call of the B_K = true instance (its device pass accepts both).
-#if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem4s<true, B_K, 4> sm;
+  __shared__ __attribute__((aligned(16))) Smem<B_K> sm;
   __shared__ int ttok[Cfg::BM];
   __shared__ float tl[Cfg::BM], tg[Cfg::BM];
   const int tiles_m = (n + Cfg::BM - 1) / Cfg::BM, tiles_n = (cw + Cfg::BN - 1) / Cfg::BN;
@@ -508,55 +495,61 @@ __global__ __launch_bounds__(Cfg::NT, 1) void lm_dz_fused_kernel(
     tl[threadIdx.x] = m < n ? lse[m] * kLog2e : 0.f;
     tg[threadIdx.x] = m < n ? g[m] : 0.f;
   }
-  f32x16_t acc[Cfg::TM][Cfg::TN];
-  gemm_core::mainloop8s<true, B_K, Cfg, 4>(acc, hn, d, wc, ldw, n, cw, m0, n0, 0, d, sm);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  f32x4_t acc[Cfg::TM][Cfg::TN];
+  gemm_core::mainloop<Cfg, true, B_K>(acc, gemm_core::Seg{hn, d, wc, ldw, 0, d}, n, cw, m0, n0,
+                                      sm);
+  const int lane = threadIdx.x & 63, wave = gemm_core::wave_id();
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   auto dz_of = [&](float a, int rl, int col) { return dz_value(a, tl[rl], tg[rl], col == ttok[rl]); };
   if (m0 + Cfg::BM > n || n0 + Cfg::BN > cw || cw % 8 != 0 || ldz % 8 != 0 ||
       ((uintptr_t)dz & 15) != 0) {
     // edge tile: element by element
 #pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
+    for (int i = 0; i < Cfg::TM; ++i) {
+      const int rl = gemm_core::acc_row<Cfg>(wm, i, lane);
+      const int m = m0 + rl;
+      if (m >= n) continue;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int rl = gemm_core::acc_row<Cfg>(wm, i, r, lane);
-        const int m = m0 + rl;
-        if (m >= n) continue;
+      for (int j = 0; j < Cfg::TN; ++j)
 #pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j) {
-          const int col = n0 + gemm_core::acc_col<Cfg>(wn, j, lane);
-          if (col >= cw) continue;
-          dz[(int64_t)m * ldz + col] = f2bf(dz_of(acc[i][j][r], rl, col));
+        for (int r = 0; r < 4; ++r) {
+          const int col = n0 + gemm_core::acc_col<Cfg>(wn, j, lane) + r;
+          if (col < cw) dz[(int64_t)m * ldz + col] = f2bf(dz_of(acc[i][j][r], rl, col));
         }
-      }
+    }
     return;
   }
   // Interior tile: dz staged as bfloat16 rows through LDS (the stage ring is
   // free once every wave is past the main loop), 128 rows per pass (32 of each
-  // wave row), then written 16 bytes per lane.
+  // wave row, four columns of a row per 8-byte write), then written 16 bytes
+  // per lane.
   constexpr int LDH = Cfg::BN + 8;   // bf16 elements per staged row
   uint16_t *stage = reinterpret_cast<uint16_t *>(&sm);
-  lds_barrier();
+  // the tile's per-row values, read before any staging write
+  float rl2[Cfg::TM], rg[Cfg::TM];
+  int rt[Cfg::TM];
 #pragma unroll
   for (int i = 0; i < Cfg::TM; ++i) {
-    // the pass's per-row values, read before any staging write
-    float rl2[16], rg[16];
-    int rt[16];
+    const int rl = gemm_core::acc_row<Cfg>(wm, i, lane);
+    rl2[i] = tl[rl];
+    rg[i] = tg[rl];
+    rt[i] = ttok[rl] - n0;
+  }
+  lds_barrier();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int rl = gemm_core::acc_row<Cfg>(wm, i, r, lane);
-      rl2[r] = tl[rl];
-      rg[r] = tg[rl];
-      rt[r] = ttok[rl] - n0;
-    }
+  for (int i = 0; i < Cfg::TM / 2; ++i) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int ls = wm * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    for (int h = 0; h < 2; ++h) {
+      const int ii = 2 * i + h, ls = wm * 32 + 16 * h + (lane & 15);
 #pragma unroll
       for (int j = 0; j < Cfg::TN; ++j) {
         const int cl = gemm_core::acc_col<Cfg>(wn, j, lane);
-        stage[ls * LDH + cl] = f2bf(dz_value(acc[i][j][r], rl2[r], rg[r], cl == rt[r]));
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          v[r] = dz_value(acc[ii][j][r], rl2[ii], rg[ii], cl + r == rt[ii]);
+        *reinterpret_cast<uint2 *>(stage + ls * LDH + cl) =
+            make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
       }
     }
     lds_barrier();
@@ -576,7 +569,6 @@ __global__ __launch_bounds__(Cfg::NT, 1) void lm_dz_fused_kernel(
     }
     lds_barrier();
   }
-#endif
 }
 
 int check_cfg(const aj_loss_cfg *c, const aj_loss_in *in, const char *name) {
