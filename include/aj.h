@@ -495,9 +495,11 @@ int aj_adamw_step(int64_t n, float *param, const float *grad, float *m, float *v
  * keeps besides the error text) and meant for a single-threaded driver.
  *   AJ_KC_MERGE      one aj_merge_timelines / aj_merge_timelines_text / aj_flatten_timelines call
  *   AJ_KC_GEMM_*     the MFMA GEMM, by operand layout (NT: both K-major;
- *                    NN: B N-major; TN: A M-major and B N-major), 8-wave
- *                    kernel (reductions shorter than 4096 per split)
- *   AJ_KC_GEMM4_*    the same layouts, 4-wave kernel (longer reductions)
+ *                    NN: B N-major; TN: A M-major and B N-major), reductions
+ *                    shorter than 4096 and products with the SwiGLU backward
+ *                    or the adapters' second segment (8-wave kernel, or the
+ *                    4-wave one of small tiles)
+ *   AJ_KC_GEMM4_*    the same layouts, longer reductions (4-wave kernels)
  *   AJ_KC_ATTN_FWD / AJ_KC_ATTN_BWD   the attention kernels of one call
  *   AJ_KC_LM_FWD     the fused logits + log-sum-exp kernel of the LM head
  *   AJ_KC_LM_DZ      the fused logits-recompute + d logits kernel (one per chunk)

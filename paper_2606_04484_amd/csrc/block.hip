@@ -61,13 +61,11 @@ BwdWs carve_bwd(const aj_block_cfg &c, int n, void *base) {
   w.delta = cv.take<float>((int64_t)c.n_q_heads * n);
   w.da = cv.take<float>(n * d);
   w.dg_part = cv.take<float>(aj::rmsnorm_bwd_part_floats(n, (int)d));
-  // split-K partials of the weight-gradient GEMMs (K = tokens)
-  size_t sk = aj::gemm_split_floats((int)d, (int)F, n);
-  sk = std::max(sk, aj::gemm_split_floats((int)(2 * F), (int)d, n));
-  sk = std::max(sk, aj::gemm_split_floats((int)d, (int)hq, n));
-  sk = std::max(sk, aj::gemm_split_floats((int)q, (int)d, n));
-  w.splitk = cv.take<float>(sk > 0 ? sk : 1);
-  w.splitk_floats = sk > 0 ? sk : 1;
+  // sums of split reductions: the weight gradients (2F x d the largest) and the
+  // products of n rows (2F columns the widest)
+  w.splitk_floats = std::max(aj::gemm_partial_floats(2 * F, std::max(d, q)),
+                             aj::gemm_partial_floats(n, 2 * F));
+  w.splitk = cv.take<float>(w.splitk_floats);
   w.bytes = cv.bytes();
   return w;
 }
@@ -97,7 +95,7 @@ struct LoraBwd {
   float *da[4], *db[4];
   float *v32;         // [n, r] d_out B
   void *vs;           // [n, r] v
-  float *partial;     // split-K partials of dA / dB
+  float *partial;     // sums of the split reductions of dA, dB and v
   size_t partial_floats;
 };
 
@@ -122,35 +120,16 @@ size_t carve_lora_saved(const aj_block_cfg &c, int r, int n, void *base, LoraFwd
   return cv.bytes();
 }
 
-// Split-K factor of the adapters' gradient GEMMs (a few output tiles, K =
-// tokens): enough splits for ~2 workgroups per CU, at least 2048 k each.
-int lora_split(int M, int N, int K) {
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  int S = (512 + tiles - 1) / tiles;
-  S = std::min(S, std::min(K / 2048, 64));
-  return S < 1 ? 1 : S;
-}
-
-size_t lora_split_floats(const aj_block_cfg &c, int r, int n) {
-  size_t f = 0;
-  for (int p = 0; p < 4; ++p) {
-    const int o = proj_out(c, p), i = proj_in(c, p);
-    const int sb = lora_split(o, r, n), sa = lora_split(r, i, n);
-    if (sb > 1) f = std::max(f, (size_t)sb * o * r);   // dB
-    if (sa > 1) f = std::max(f, (size_t)sa * r * i);   // dA
-  }
-  return f;
-}
-
 // The adapters' part of the backward workspace, placed after the block's own.
 size_t carve_lora_bwd(const aj_block_cfg &c, int r, int n, void *base, LoraBwd *lb) {
   const size_t es = c.dtype == AJ_BF16 ? 2 : 4;
   aj::Carver cv(base);
   float *v32 = cv.take<float>((int64_t)n * r);
   void *vs = cv.take<char>((int64_t)n * r * es);
-  const size_t sk = lora_split_floats(c, r, n);
-  float *part = cv.take<float>(sk > 0 ? sk : 1);
-  if (lb) { lb->v32 = v32; lb->vs = vs; lb->partial = part; lb->partial_floats = sk > 0 ? sk : 1; }
+  const size_t sk = std::max(aj::gemm_partial_floats(r, std::max(2 * c.d_ff, proj_out(c, kQkv))),
+                             aj::gemm_partial_floats(n, r));
+  float *part = cv.take<float>(sk);
+  if (lb) { lb->v32 = v32; lb->vs = vs; lb->partial = part; lb->partial_floats = sk; }
   return cv.bytes();
 }
 
@@ -184,7 +163,7 @@ int lora_grads(const aj_block_cfg &c, const LoraBwd &lb, int p, const T *d_out, 
   Gemm g;   // dB [n_out, r] += d_out^T u
   g.M = n_out; g.N = r; g.K = n; g.A = d_out; g.lda = n_out; g.a_kmajor = false;
   g.B = lb.u[p]; g.ldb = r; g.b_kmajor = false; g.C = lb.db[p]; g.ldc = r;
-  g.out = OUT_ACCUM_F32; g.split_k = lora_split(g.M, g.N, g.K); g.partial = lb.partial;
+  g.out = OUT_ACCUM_F32; g.partial = lb.partial;
   g.partial_cap = lb.partial_floats;
   if ((rc = gemm<T>(g, st))) return rc;
   g = Gemm();   // v [n, r] = (d_out B)_s
@@ -195,7 +174,7 @@ int lora_grads(const aj_block_cfg &c, const LoraBwd &lb, int p, const T *d_out, 
   g = Gemm();   // dA [r, k_in] += v^T in
   g.M = r; g.N = k_in; g.K = n; g.A = lb.vs; g.lda = r; g.a_kmajor = false;
   g.B = in; g.ldb = k_in; g.b_kmajor = false; g.C = lb.da[p]; g.ldc = k_in;
-  g.out = OUT_ACCUM_F32; g.split_k = lora_split(g.M, g.N, g.K); g.partial = lb.partial;
+  g.out = OUT_ACCUM_F32; g.partial = lb.partial;
   g.partial_cap = lb.partial_floats;
   return gemm<T>(g, st);
 }
@@ -297,7 +276,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   if (!frozen) {
     g.M = d; g.N = F; g.K = n; g.A = dy_t; g.lda = d; g.a_kmajor = false;
     g.B = sv.s; g.ldb = F; g.b_kmajor = false; g.C = gr.w_down; g.ldc = F;
-    g.out = OUT_ACCUM_F32; g.split_k = gemm_split_k(g.M, g.N, g.K); g.partial = ws.splitk;
+    g.out = OUT_ACCUM_F32; g.partial = ws.splitk;
     g.partial_cap = ws.splitk_floats;
     if ((r = gemm<T>(g, st))) return r;
   }
@@ -320,7 +299,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
     g = Gemm();
     g.M = 2 * F; g.N = d; g.K = n; g.A = ws.dgu; g.lda = 2 * F; g.a_kmajor = false;
     g.B = sv.b; g.ldb = d; g.b_kmajor = false; g.C = gr.w_gate_up; g.ldc = d;
-    g.out = OUT_ACCUM_F32; g.split_k = gemm_split_k(g.M, g.N, g.K); g.partial = ws.splitk;
+    g.out = OUT_ACCUM_F32; g.partial = ws.splitk;
     g.partial_cap = ws.splitk_floats;
     if ((r = gemm<T>(g, st))) return r;
   }
@@ -339,7 +318,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
     g = Gemm();
     g.M = d; g.N = hq; g.K = n; g.A = dx1_t; g.lda = d; g.a_kmajor = false;
     g.B = sv.o; g.ldb = hq; g.b_kmajor = false; g.C = gr.w_o; g.ldc = hq;
-    g.out = OUT_ACCUM_F32; g.split_k = gemm_split_k(g.M, g.N, g.K); g.partial = ws.splitk;
+    g.out = OUT_ACCUM_F32; g.partial = ws.splitk;
     g.partial_cap = ws.splitk_floats;
     if ((r = gemm<T>(g, st))) return r;
   }
@@ -358,7 +337,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
     g = Gemm();
     g.M = qdim; g.N = d; g.K = n; g.A = ws.dqkv; g.lda = qdim; g.a_kmajor = false;
     g.B = sv.a; g.ldb = d; g.b_kmajor = false; g.C = gr.w_qkv; g.ldc = d;
-    g.out = OUT_ACCUM_F32; g.split_k = gemm_split_k(g.M, g.N, g.K); g.partial = ws.splitk;
+    g.out = OUT_ACCUM_F32; g.partial = ws.splitk;
     g.partial_cap = ws.splitk_floats;
     if ((r = gemm<T>(g, st))) return r;
   }

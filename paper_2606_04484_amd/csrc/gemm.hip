@@ -39,25 +39,24 @@ using gemm_core::Seg;
 // Output modes of the epilogue's fast path (interior tiles, aligned rows).
 enum { kEpPartial, kEpAccum, kEpF32, kEpF32R, kEpBf16, kEpBf16R, kEpSwiglu };
 
-// One pass of the fast epilogue: the 64 staged rows (32 of each wave row)
-// x 256 columns, 4 columns per thread and instruction; every LDS read of the
-// pass is issued before the first store.
+// One pass of the fast epilogue: the staged rows (32 of each wave row), 4
+// columns per thread and instruction; every LDS read of the pass is issued
+// before the first store.
 template <int MODE, typename Cfg>
 AJ_DEV void store_pass(const float *stage, int i, int m0, int n0, int64_t ldo, float *P,
                        const EpArgs &ep) {
-  static_assert(Cfg::WTM == 128 && Cfg::BN == 256, "two wave rows of 128, 256 columns");
-  constexpr int LDW = Cfg::BN + 4;
-  constexpr int Q = 64 * 64 / Cfg::NT;
+  constexpr int LDW = Cfg::BN + 4, C4 = Cfg::BN / 4;
+  constexpr int Q = 32 * Cfg::WM * C4 / Cfg::NT;
   float4 v[Q];
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const int c = threadIdx.x + Cfg::NT * q;
-    v[q] = *reinterpret_cast<const float4 *>(stage + (c >> 6) * LDW + (c & 63) * 4);
+    v[q] = *reinterpret_cast<const float4 *>(stage + (c / C4) * LDW + (c % C4) * 4);
   }
   auto offset = [&](int q) {
     const int c = threadIdx.x + Cfg::NT * q;
-    const int row = c >> 6;
-    return (int64_t)(m0 + (row >> 5) * 128 + 32 * i + (row & 31)) * ldo + n0 + (c & 63) * 4;
+    const int row = c / C4;
+    return (int64_t)(m0 + (row >> 5) * Cfg::WTM + 32 * i + (row & 31)) * ldo + n0 + (c % C4) * 4;
   };
   if constexpr (MODE == kEpAccum || MODE == kEpF32R) {
     const float *src = MODE == kEpAccum ? (const float *)ep.C : (const float *)ep.R;
@@ -128,17 +127,79 @@ AJ_DEV void epi_barrier() {
   gemm_core::bar_nofence();
 }
 
+// The epilogue of four consecutive columns (m, n) .. (m, n + 3) of the output, m
+// and n inside it, columns past N left out.
+AJ_DEV void store4(const EpArgs &ep, int m, int n, const float4 &v) {
+  const int64_t o = (int64_t)m * ep.ldc + n;
+  const float vv[4] = {v.x, v.y, v.z, v.w};
+  if (ep.gu) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (n + e >= ep.N) break;
+      float dg, du;
+      swiglu_grad(vv[e], bf2f(ep.gu[o + e]), bf2f(ep.gu[o + e + ep.N]), dg, du);
+      ((bf16_t *)ep.C)[o + e] = f2bf(dg);
+      ((bf16_t *)ep.C)[o + e + ep.N] = f2bf(du);
+    }
+  } else if (ep.vec && n + 4 <= ep.N) {
+    if (ep.c_f32) {
+      float4 *cp = reinterpret_cast<float4 *>((float *)ep.C + o);
+      float4 w = v;
+      if (ep.accum || ep.R) {
+        const float4 u = ep.accum ? *cp : *reinterpret_cast<const float4 *>((const float *)ep.R + o);
+        w.x += u.x; w.y += u.y; w.z += u.z; w.w += u.w;
+      }
+      *cp = w;
+    } else {
+      float w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
+      if (ep.R) {
+        const uint2 u = *reinterpret_cast<const uint2 *>((const bf16_t *)ep.R + o);
+        w0 += __uint_as_float(u.x << 16); w1 += __uint_as_float(u.x & 0xffff0000u);
+        w2 += __uint_as_float(u.y << 16); w3 += __uint_as_float(u.y & 0xffff0000u);
+      }
+      *reinterpret_cast<uint2 *>((bf16_t *)ep.C + o) = make_uint2(f2bf2(w0, w1), f2bf2(w2, w3));
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (n + e >= ep.N) break;
+      if (ep.accum) ((float *)ep.C)[o + e] += vv[e];
+      else if (ep.c_f32) ((float *)ep.C)[o + e] = vv[e] + (ep.R ? ((const float *)ep.R)[o + e] : 0.f);
+      else ((bf16_t *)ep.C)[o + e] = f2bf(vv[e] + (ep.R ? bf2f(((const bf16_t *)ep.R)[o + e]) : 0.f));
+    }
+  }
+}
+
+// Which output tiles a launch runs whole and which in pieces: tiles [0, whole)
+// of the walk take one workgroup each; each of the rest takes `split`, on
+// ranges of k_piece, whose float32 sums go to `partial` (a BM x BN block per
+// piece, pieces of one range side by side) for gemm_pieces_kernel to add up.
+struct Pieces {
+  int whole, rest, split, k_piece;
+  float *partial;
+};
+
 // Shared body of the GEMM kernels: main loop of configuration Cfg (and the
 // second segment's, SEG2), then the epilogue through LDS.
 template <bool A_K, bool B_K, typename Cfg, bool SEG2 = false>
-AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int64_t lda,
-                      const bf16_t *B, int64_t ldb, const EpArgs &ep, float *partial,
+AJ_DEV void gemm_tile(int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B,
+                      int64_t ldb, const EpArgs &ep, const Pieces &pc,
                       gemm_core::Smem<Cfg, A_K, B_K> &sm, const Seg &s2 = Seg{}) {
   const int tiles_m = (M + Cfg::BM - 1) / Cfg::BM, tiles_n = (N + Cfg::BN - 1) / Cfg::BN;
-  const gemm_core::TileIdx ti = gemm_core::tile_of(blockIdx.x, gridDim.x, tiles_m, tiles_n);
+  int t, kbeg = 0, kend = K;
+  float *P = nullptr;
+  if ((int)blockIdx.x < pc.whole) {
+    t = gemm_core::xcd_item(blockIdx.x, pc.whole);
+  } else {
+    // an XCD's pieces are of neighbouring tiles over one range of k
+    const int p = gemm_core::xcd_item(blockIdx.x - pc.whole, pc.rest * pc.split);
+    t = pc.whole + p % pc.rest;
+    kbeg = (p / pc.rest) * pc.k_piece;
+    kend = min(K, kbeg + pc.k_piece);
+    P = pc.partial + (int64_t)p * (Cfg::BM * Cfg::BN);
+  }
+  const gemm_core::TileIdx ti = gemm_core::tile_at(t, tiles_m, tiles_n);
   const int m0 = ti.tm * Cfg::BM, n0 = ti.tn * Cfg::BN;
-  const int kbeg = blockIdx.z * k_per_split;
-  const int kend = min(K, kbeg + k_per_split);
   const int lane = threadIdx.x & 63, wave = gemm_core::wave_id();
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   f32x4_t acc[Cfg::TM][Cfg::TN];
@@ -150,14 +211,15 @@ AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int
   // tiles) at a time: a lane's four consecutive columns of a row go out as one
   // 16-byte write, then rows are stored 4 columns per lane.  The padding of 4
   // floats per row puts the 16 rows of a write on different banks.
-  // Interior tiles with aligned rows take a pass specialised to the output
-  // mode (no per-element branches, the pass's LDS reads issued together);
-  // edge tiles go element by element.
+  // Pieces, and interior tiles with aligned rows, take a pass specialised to
+  // the output mode (no per-element branches, the pass's LDS reads issued
+  // together); edge tiles go four columns at a time.
   float *stage = reinterpret_cast<float *>(&sm);
-  constexpr int LDW = Cfg::BN + 4;
-  float *P = partial ? partial + (int64_t)blockIdx.z * M * N : nullptr;
-  const int64_t ldo = partial ? N : ep.ldc;
-  const bool fast = ep.vec && m0 + Cfg::BM <= M && n0 + Cfg::BN <= N;
+  constexpr int LDW = Cfg::BN + 4, C4 = Cfg::BN / 4;
+  // the SwiGLU pass is for tiles of 128 accumulators and fewer: with 256 it
+  // pushes the epilogue past full unrolling and the accumulators into scratch
+  constexpr bool kSwiglu = Cfg::TM * Cfg::TN <= 32;
+  const bool fast = P || (ep.vec && m0 + Cfg::BM <= M && n0 + Cfg::BN <= N && (kSwiglu || !ep.gu));
   const int mode = P ? kEpPartial
                    : ep.gu ? kEpSwiglu
                    : ep.accum ? kEpAccum
@@ -173,97 +235,40 @@ AJ_DEV void gemm_tile(int M, int N, int K, int k_per_split, const bf16_t *A, int
                                      gemm_core::acc_col<Cfg>(wn, j, lane)) = acc[2 * i + h][j];
     epi_barrier();
     if (fast) {
+      const int64_t ldo = ep.ldc;
       switch (mode) {
-        case kEpPartial: store_pass<kEpPartial, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
+        case kEpPartial: store_pass<kEpPartial, Cfg>(stage, i, 0, 0, Cfg::BN, P, ep); break;
         case kEpAccum: store_pass<kEpAccum, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
         case kEpF32: store_pass<kEpF32, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
         case kEpF32R: store_pass<kEpF32R, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
         case kEpBf16: store_pass<kEpBf16, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
         case kEpSwiglu:
-          // 8-wave tiles only: in the 4-wave one the extra pass pushes the
-          // epilogue past full unrolling and the accumulator into scratch
-          if constexpr (Cfg::NT == 512) store_pass<kEpSwiglu, Cfg>(stage, i, m0, n0, ldo, P, ep);
+          if constexpr (kSwiglu) store_pass<kEpSwiglu, Cfg>(stage, i, m0, n0, ldo, P, ep);
           break;
         default: store_pass<kEpBf16R, Cfg>(stage, i, m0, n0, ldo, P, ep); break;
       }
-      epi_barrier();
-      continue;
-    }
+    } else {
 #pragma unroll 4
-    for (int q = 0; q < 64 * 64 / Cfg::NT; ++q) {
-      const int c = threadIdx.x + Cfg::NT * q;
-      const int row = c >> 6, c4 = (c & 63) * 4;
-      const int m = m0 + (row >> 5) * 128 + 32 * i + (row & 31), n = n0 + c4;
-      if (m >= M || n >= N) continue;
-      const float4 v = *reinterpret_cast<const float4 *>(stage + row * LDW + c4);
-      const int64_t o = (int64_t)m * ldo + n;
-      if (ep.gu) {
-        const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (n + e >= N) break;
-          float dg, du;
-          swiglu_grad(vv[e], bf2f(ep.gu[o + e]), bf2f(ep.gu[o + e + N]), dg, du);
-          ((bf16_t *)ep.C)[o + e] = f2bf(dg);
-          ((bf16_t *)ep.C)[o + e + N] = f2bf(du);
-        }
-        continue;
-      }
-      if (ep.vec && n + 4 <= N) {
-        if (P) {
-          *reinterpret_cast<float4 *>(P + o) = v;
-        } else if (ep.c_f32) {
-          float4 *cp = reinterpret_cast<float4 *>((float *)ep.C + o);
-          float4 w = v;
-          if (ep.accum) {
-            const float4 u = *cp;
-            w.x += u.x; w.y += u.y; w.z += u.z; w.w += u.w;
-          } else if (ep.R) {
-            const float4 u = *reinterpret_cast<const float4 *>((const float *)ep.R + o);
-            w.x += u.x; w.y += u.y; w.z += u.z; w.w += u.w;
-          }
-          *cp = w;
-        } else {
-          float w0 = v.x, w1 = v.y, w2 = v.z, w3 = v.w;
-          if (ep.R) {
-            const uint2 u = *reinterpret_cast<const uint2 *>((const bf16_t *)ep.R + o);
-            w0 += __uint_as_float(u.x << 16); w1 += __uint_as_float(u.x & 0xffff0000u);
-            w2 += __uint_as_float(u.y << 16); w3 += __uint_as_float(u.y & 0xffff0000u);
-          }
-          uint2 out;
-          out.x = f2bf2(w0, w1);
-          out.y = f2bf2(w2, w3);
-          *reinterpret_cast<uint2 *>((bf16_t *)ep.C + o) = out;
-        }
-      } else {
-        const float vv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (n + e >= N) break;
-          const float x = vv[e];
-          if (P) {
-            P[o + e] = x;
-          } else if (ep.accum) {
-            ((float *)ep.C)[o + e] += x;
-          } else if (ep.c_f32) {
-            ((float *)ep.C)[o + e] = x + (ep.R ? ((const float *)ep.R)[o + e] : 0.f);
-          } else {
-            ((bf16_t *)ep.C)[o + e] = f2bf(x + (ep.R ? bf2f(((const bf16_t *)ep.R)[o + e]) : 0.f));
-          }
-        }
+      for (int q = 0; q < 32 * Cfg::WM * C4 / Cfg::NT; ++q) {
+        const int c = threadIdx.x + Cfg::NT * q;
+        const int row = c / C4, c4 = (c % C4) * 4;
+        const int m = m0 + (row >> 5) * Cfg::WTM + 32 * i + (row & 31), n = n0 + c4;
+        if (m < M && n < N)
+          store4(ep, m, n, *reinterpret_cast<const float4 *>(stage + row * LDW + c4));
       }
     }
     epi_barrier();
   }
 }
 
-// Cfg8 is the default, Cfg4 takes reductions of kLongK and more.
+// Cfg8 is the default, Cfg4 takes reductions of kLongK and more, CfgS (two
+// workgroups to a CU) products of few tiles.
 template <typename Cfg, bool A_K, bool B_K>
-__global__ __launch_bounds__(Cfg::NT, 1) void gemm_mfma_kernel(
-    int M, int N, int K, int k_per_split, const bf16_t *A, int64_t lda, const bf16_t *B,
-    int64_t ldb, EpArgs ep, float *partial) {
+__global__ __launch_bounds__(Cfg::NT, Cfg::BM == 128 ? 2 : 1) void gemm_mfma_kernel(
+    int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B, int64_t ldb, EpArgs ep,
+    Pieces pc) {
   __shared__ __attribute__((aligned(16))) gemm_core::Smem<Cfg, A_K, B_K> sm;
-  gemm_tile<A_K, B_K, Cfg>(M, N, K, k_per_split, A, lda, B, ldb, ep, partial, sm);
+  gemm_tile<A_K, B_K, Cfg>(M, N, K, A, lda, B, ldb, ep, pc, sm);
 }
 
 // The 8-wave kernel with a second reduction segment with the operand layouts of
@@ -271,9 +276,35 @@ __global__ __launch_bounds__(Cfg::NT, 1) void gemm_mfma_kernel(
 template <bool A_K, bool B_K>
 __global__ __launch_bounds__(gemm_core::Cfg8::NT, 1) void gemm_mfma_seg2_kernel(
     int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B, int64_t ldb, Seg s2,
-    EpArgs ep) {
+    EpArgs ep, Pieces pc) {
   __shared__ __attribute__((aligned(16))) gemm_core::Smem<gemm_core::Cfg8, A_K, B_K> sm;
-  gemm_tile<A_K, B_K, gemm_core::Cfg8, true>(M, N, K, K, A, lda, B, ldb, ep, nullptr, sm, s2);
+  gemm_tile<A_K, B_K, gemm_core::Cfg8, true>(M, N, K, A, lda, B, ldb, ep, pc, sm, s2);
+}
+
+// The pieces of each split tile added up in the order of their k ranges, then
+// the epilogue.  One workgroup per 4096 outputs of a tile, 4 columns per thread
+// and load; the partials were written just before and mostly sit in the
+// last-level cache.
+template <int BM, int BN>
+__global__ __launch_bounds__(256) void gemm_pieces_kernel(EpArgs ep, Pieces pc) {
+  constexpr int PER = BM * BN / 4096;
+  const int r = blockIdx.x / PER, part = blockIdx.x % PER;
+  const int tiles_m = (ep.M + BM - 1) / BM, tiles_n = (ep.N + BN - 1) / BN;
+  const gemm_core::TileIdx ti = gemm_core::tile_at(pc.whole + r, tiles_m, tiles_n);
+  const float *P = pc.partial + (int64_t)r * (BM * BN);
+  const int64_t step = (int64_t)pc.rest * (BM * BN);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int e = part * 4096 + (q * 256 + (int)threadIdx.x) * 4;
+    const int m = ti.tm * BM + e / BN, n = ti.tn * BN + e % BN;
+    if (m >= ep.M || n >= ep.N) continue;
+    float4 v = *reinterpret_cast<const float4 *>(P + e);
+    for (int z = 1; z < pc.split; ++z) {
+      const float4 u = *reinterpret_cast<const float4 *>(P + z * step + e);
+      v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+    }
+    store4(ep, m, n, v);
+  }
 }
 
 constexpr int kLongK = 4096;
@@ -351,57 +382,106 @@ __global__ __launch_bounds__(256) void gemm_simple_kernel(int M, int N, int K, i
 }
 
 template <bool A_K, bool B_K>
-void launch_mfma(const Gemm &g, const EpArgs &ep, int kps, bool long_k, hipStream_t s) {
-  const int tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
-  dim3 grid(tiles, 1, g.split_k);
-  float *part = g.split_k > 1 ? g.partial : nullptr;
+void launch_mfma(const Gemm &g, const EpArgs &ep, const GemmPlan &pl, hipStream_t s) {
+  const Pieces pc{pl.whole, pl.tiles - pl.whole, pl.split, pl.k_piece, g.partial};
+  const int grid = pc.whole + pc.rest * pc.split;
+  const bf16_t *A = (const bf16_t *)g.A, *B = (const bf16_t *)g.B;
   if (g.K2 > 0) {
     const Seg s2{(const bf16_t *)g.A2, g.lda2, (const bf16_t *)g.B2, g.ldb2, 0, g.K2};
-    gemm_mfma_seg2_kernel<A_K, B_K><<<tiles, gemm_core::Cfg8::NT, 0, s>>>(
-        g.M, g.N, g.K, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, s2, ep);
-    return;
-  }
-  if (long_k)
+    gemm_mfma_seg2_kernel<A_K, B_K><<<grid, gemm_core::Cfg8::NT, 0, s>>>(g.M, g.N, g.K, A, g.lda,
+                                                                       B, g.ldb, s2, ep, pc);
+  } else if (pl.tile == 128) {
+    gemm_mfma_kernel<gemm_core::CfgS, A_K, B_K><<<grid, gemm_core::CfgS::NT, 0, s>>>(
+        g.M, g.N, g.K, A, g.lda, B, g.ldb, ep, pc);
+  } else if (pl.long_k) {
     gemm_mfma_kernel<gemm_core::Cfg4, A_K, B_K><<<grid, gemm_core::Cfg4::NT, 0, s>>>(
-        g.M, g.N, g.K, kps, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, ep, part);
-  else
+        g.M, g.N, g.K, A, g.lda, B, g.ldb, ep, pc);
+  } else {
     gemm_mfma_kernel<gemm_core::Cfg8, A_K, B_K><<<grid, gemm_core::Cfg8::NT, 0, s>>>(
-        g.M, g.N, g.K, kps, (const bf16_t *)g.A, g.lda, (const bf16_t *)g.B, g.ldb, ep, part);
+        g.M, g.N, g.K, A, g.lda, B, g.ldb, ep, pc);
+  }
+  if (pc.rest == 0 || pc.split <= 1) return;
+  if (pl.tile == 128) gemm_pieces_kernel<128, 128><<<pc.rest * 4, 256, 0, s>>>(ep, pc);
+  else gemm_pieces_kernel<256, 256><<<pc.rest * 16, 256, 0, s>>>(ep, pc);
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
+// Predicted times, in us, of one round of workgroups over a reduction of k.
+// 256 x 256 tiles, one workgroup per CU: 7.5 us of prologue and epilogue, then
+// 15.4 ns per k while few CUs work, 22.8 ns with all 256 (copy rate and power
+// shared).  128 x 128 tiles, two per CU: 8.6 ns per k with one on a CU, 16.5
+// with two.  Adding up pieces: a launch and its bytes.  Fitted to NN and TN
+// products of M 700 .. 19437, N 1536 .. 37888, K 1536 .. 32768, which it gives
+// to 10 %.
+static double round_256(int tiles, double k) {
+  const double busy = tiles <= 64 ? 0.0 : (tiles - 64) / 192.0;
+  return 7.5 + k * (0.0154 + 0.0074 * busy);
+}
+static double round_128(int tiles, double k) {
+  return tiles <= 256 ? 4.5 + 0.0086 * k : 6.0 + 0.0165 * k;
+}
+static double rounds(int tile, int tiles, double k) {
+  const int per = tile == 256 ? 256 : 512, full = tiles / per, rem = tiles % per;
+  auto one = [&](int t) { return tile == 256 ? round_256(t, k) : round_128(t, k); };
+  return (full ? full * one(per) : 0.0) + (rem ? one(rem) : 0.0);
+}
+
+// The fastest of: every 256 x 256 tile whole; the tiles past the last full
+// round of 256 in pieces (all of them, when there are fewer than 256 tiles);
+// 128 x 128 tiles, whole or in pieces.  Measured either side of the lines (NN):
+//   2347 x 1536, K 1536: 256 whole 31.2, 128 whole 17.8 us
+//   2347 x 1536, K 8960: 256 whole 138.7, 256 in 4 pieces 70.4, 128 whole 80.2 us
+//   700 x 1536, K 8960: 256 in 8 pieces 40.0, 128 in 3 pieces 36.3 us
+//   14500 x 1536, K 8960 (342 tiles): whole 376.8, last 86 in 2 pieces 312.2 us
+//   19437 x 3584, K 18944 (1064 tiles): whole 2140, last 40 in 6 pieces 1879 us
+//   700 x 17920, K 1536 (210 tiles): 256 whole 42.2, 128 whole 48.1 us
+GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool whole_only, bool swiglu) {
+  auto tiles_of = [&](int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
+  GemmPlan best{256, K >= kLongK && !swiglu && !whole_only, tiles_of(256), tiles_of(256), 1, K};
+  if (whole_only || K <= 0) return best;
+  double t_best = rounds(256, best.tiles, K);
+  for (int tile = 256; tile >= 128; tile /= 2) {
+    const int tiles = tiles_of(tile);
+    if (tile == 128) {
+      const double t = rounds(128, tiles, K);
+      if (t < t_best) t_best = t, best = {128, false, tiles, tiles, 1, K};
+    }
+    // pieces: of the last, partial round of 256 x 256 tiles, or of every tile
+    const int whole = tile == 256 ? tiles / 256 * 256 : 0, rest = tiles - whole;
+    if (rest == 0 || (tile == 128 && rest > 512)) continue;
+    for (int S = 2; S <= kMaxSplit && K / S >= 256; ++S) {
+      const int64_t pieces = (int64_t)rest * S;
+      if ((size_t)pieces * tile * tile > partial_cap || pieces > 1024) break;
+      const int k_piece = ((K + S - 1) / S + 31) / 32 * 32;
+      const double t = rounds(tile, whole, K) + rounds(tile, (int)pieces, k_piece) + 6.0 +
+                       0.03 * pieces * tile * tile / 65536.0;
+      if (t < t_best) {
+        t_best = t;
+        best = {tile, tile == 256 && !swiglu && (whole ? K : k_piece) >= kLongK, tiles, whole, S, k_piece};
+      }
+    }
+  }
+  return best;
+}
+
 template <typename T>
 int gemm(const Gemm &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return AJ_OK;
-  if (g.split_k > 1 && !g.partial) return fail(AJ_ERR_WORKSPACE, "gemm: split-K without workspace");
-  if (g.split_k > 1 && (size_t)g.split_k * g.M * g.N > g.partial_cap)
-    return fail(AJ_ERR_WORKSPACE, "gemm: split-K %d of %d x %d needs %zu floats, workspace has %zu",
-                g.split_k, g.M, g.N, (size_t)g.split_k * g.M * g.N, g.partial_cap);
-  if (g.K2 > 0 && (g.split_k > 1 || !g.A2 || !g.B2))
-    return fail(AJ_ERR_UNSUPPORTED, "gemm: a second segment needs its operands and no split-K");
+  if (g.K2 > 0 && (!g.A2 || !g.B2))
+    return fail(AJ_ERR_UNSUPPORTED, "gemm: a second segment needs its operands");
   EpArgs ep{g.M, g.N, g.C, g.ldc, g.c_f32 ? 1 : 0, g.out == OUT_ACCUM_F32 ? 1 : 0, g.R, 0,
             (const bf16_t *)g.swiglu_gu};
-  if (g.swiglu_gu && (sizeof(T) != 2 || g.split_k > 1 || ep.accum || ep.c_f32 || g.R ||
-                      g.ldc < 2 * (int64_t)g.N))
-    return fail(AJ_ERR_UNSUPPORTED, "gemm: SwiGLU epilogue needs bf16 C [n, 2N], no split-K, "
+  if (g.swiglu_gu && (sizeof(T) != 2 || ep.accum || ep.c_f32 || g.R || g.ldc < 2 * (int64_t)g.N))
+    return fail(AJ_ERR_UNSUPPORTED, "gemm: SwiGLU epilogue needs bf16 C [n, 2N], no "
                 "accumulation or residual");
   if (ep.accum) ep.c_f32 = 1;
   {
     const uintptr_t al = ep.c_f32 ? 15 : 7;
-    const bool split = g.split_k > 1;
-    ep.vec = split ? (g.N % 4 == 0 && ((uintptr_t)g.partial & 15) == 0)
-                   : (g.ldc % 4 == 0 && ((uintptr_t)g.C & al) == 0 && ((uintptr_t)g.R & al) == 0 &&
-                      (!g.swiglu_gu || (g.N % 4 == 0 && ((uintptr_t)g.swiglu_gu & 7) == 0)));
-  }
-  const int S = g.split_k > 1 ? g.split_k : 1;
-  int kps = (g.K + S - 1) / S;
-  kps = (kps + 63) / 64 * 64;
-  if (g.K <= 0) {
-    // empty reduction: C = R (or unchanged when accumulating)
-    kps = 0;
+    ep.vec = g.ldc % 4 == 0 && ((uintptr_t)g.C & al) == 0 && ((uintptr_t)g.R & al) == 0 &&
+             (!g.swiglu_gu || (g.N % 4 == 0 && ((uintptr_t)g.swiglu_gu & 7) == 0));
   }
   bool mfma = false;
   if constexpr (sizeof(T) == 2) {
@@ -415,34 +495,35 @@ int gemm(const Gemm &g, hipStream_t s) {
              aligned16(g.A2) && aligned16(g.B2);
     }
   }
+  const size_t cap = g.partial && aligned16(g.partial) ? g.partial_cap : 0;
   if (mfma) {
-    // the second segment and the SwiGLU epilogue run 8-wave
-    const bool long_k = kps >= kLongK && g.K2 == 0 && !g.swiglu_gu;
+    const GemmPlan pl = gemm_plan(g.M, g.N, g.K, cap, g.K2 > 0, g.swiglu_gu != nullptr);
     int kc = g.a_kmajor ? (g.b_kmajor ? AJ_KC_GEMM_NT : AJ_KC_GEMM_NN) : AJ_KC_GEMM_TN;
-    if (long_k) kc += AJ_KC_GEMM4_NT - AJ_KC_GEMM_NT;
+    if (g.K >= kLongK && g.K2 == 0 && !g.swiglu_gu) kc += AJ_KC_GEMM4_NT - AJ_KC_GEMM_NT;
     const int tk =
         timing_begin(s, kc, g.recompute ? 0.0 : 2.0 * g.M * g.N * ((double)g.K + g.K2));
-    if (g.a_kmajor && g.b_kmajor) launch_mfma<true, true>(g, ep, kps, long_k, s);
-    else if (g.a_kmajor) launch_mfma<true, false>(g, ep, kps, long_k, s);
-    else if (g.b_kmajor) launch_mfma<false, true>(g, ep, kps, long_k, s);
-    else launch_mfma<false, false>(g, ep, kps, long_k, s);
+    if (g.a_kmajor && g.b_kmajor) launch_mfma<true, true>(g, ep, pl, s);
+    else if (g.a_kmajor) launch_mfma<true, false>(g, ep, pl, s);
+    else if (g.b_kmajor) launch_mfma<false, true>(g, ep, pl, s);
+    else launch_mfma<false, false>(g, ep, pl, s);
     timing_end(s, tk);
-  } else {
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, S);
-    gemm_simple_kernel<T><<<grid, 256, 0, s>>>(g.M, g.N, g.K, kps, (const T *)g.A, g.lda,
-                                               g.a_kmajor, (const T *)g.B, g.ldb, g.b_kmajor, ep,
-                                               S > 1 ? g.partial : nullptr, (const T *)g.A2,
-                                               g.lda2, (const T *)g.B2, g.ldb2, g.K2);
+    return check_launch("gemm");
   }
-  int st = check_launch("gemm");
-  if (st != AJ_OK) return st;
-  if (S > 1) {
-    // fixed-order sum of the split partials into C (float32)
-    if (g.ldc != g.N) return fail(AJ_ERR_UNSUPPORTED, "gemm: split-K needs ldc == N");
-    splitk_reduce(g.partial, S, (int64_t)g.M * g.N, (float *)g.C, ep.accum != 0, s);
-    st = check_launch("gemm split-K reduce");
+  // the plain kernel splits float32 outputs stored without gaps
+  int S = 1;
+  if (ep.c_f32 && !ep.R && g.ldc == g.N && g.K2 == 0) {
+    S = gemm_split_k(g.M, g.N, g.K);
+    if ((size_t)S * g.M * g.N > cap) S = 1;
   }
-  return st;
+  const int kps = g.K <= 0 ? 0 : ((g.K + S - 1) / S + 63) / 64 * 64;   // empty: C = R
+  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, S);
+  gemm_simple_kernel<T><<<grid, 256, 0, s>>>(g.M, g.N, g.K, kps, (const T *)g.A, g.lda,
+                                             g.a_kmajor, (const T *)g.B, g.ldb, g.b_kmajor, ep,
+                                             S > 1 ? g.partial : nullptr, (const T *)g.A2,
+                                             g.lda2, (const T *)g.B2, g.ldb2, g.K2);
+  // fixed-order sum of the split partials into C
+  if (S > 1) splitk_reduce(g.partial, S, (int64_t)g.M * g.N, (float *)g.C, ep.accum != 0, s);
+  return check_launch("gemm");
 }
 
 template int gemm<float>(const Gemm &, hipStream_t);

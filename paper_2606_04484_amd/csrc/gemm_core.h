@@ -36,10 +36,15 @@ constexpr int kXcds = 8;
 
 struct TileIdx { int tm, tn; };
 
-AJ_DEV TileIdx tile_of(int wg, int nwg, int tiles_m, int tiles_n) {
+// Workgroups are dealt to the XCDs round robin: the XCD of workgroup wg of nwg
+// walks a contiguous run of items.
+AJ_DEV int xcd_item(int wg, int nwg) {
   const int per = nwg / kXcds, rem = nwg % kXcds;
   const int xcd = wg % kXcds, idx = wg / kXcds;
-  const int t = xcd * per + (xcd < rem ? xcd : rem) + idx;
+  return xcd * per + (xcd < rem ? xcd : rem) + idx;
+}
+// Tile number t of the walk.
+AJ_DEV TileIdx tile_at(int t, int tiles_m, int tiles_n) {
   // a skinny product runs whole tile rows (or columns) side by side, so that
   // each operand tile is fetched once for all the tiles that share it
   if (tiles_n <= 16) return {t / tiles_n, t % tiles_n};
@@ -50,7 +55,9 @@ AJ_DEV TileIdx tile_of(int wg, int nwg, int tiles_m, int tiles_n) {
   const int r = t % span;
   return {first_m + r % gm, r / gm};
 }
-
+AJ_DEV TileIdx tile_of(int wg, int nwg, int tiles_m, int tiles_n) {
+  return tile_at(xcd_item(wg, nwg), tiles_m, tiles_n);
+}
 
 template <int BM_, int BN_, int WM_, int WN_>
 struct MfmaCfg {
@@ -70,6 +77,9 @@ using CfgWide = MfmaCfg<256, 256, 4, 2>;
 // LDS per MFMA; used for long reductions, where its heavier per-tile prologue
 // and epilogue are amortised.
 using Cfg4 = MfmaCfg<256, 256, 2, 2>;
+// A quarter of that tile, four waves of 64x64, two workgroups to a CU: products
+// with too few 256x256 tiles to fill the chip.
+using CfgS = MfmaCfg<128, 128, 2, 2>;
 
 constexpr int kBK = 32;       // k-step
 constexpr int kStages = 4;    // LDS stages: the copies of a k-step run four steps ahead

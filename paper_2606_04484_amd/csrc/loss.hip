@@ -25,7 +25,7 @@ namespace {
 struct LossWs {
   float *z, *run_m, *run_s, *zt, *part, *g, *dhn, *dg_part;
   float2 *tile_ms;        // fused forward: per (row, 256-column tile) (max, sum of exp), log2 units
-  float *splitk;          // split-K partials of the dW_vocab GEMM
+  float *splitk;          // sums of the split reductions of d hidden and d W
   size_t splitk_floats;
   void *dz;
   int32_t *tpos, *trow;   // targets clamped into the documented range, and their h rows
@@ -71,12 +71,9 @@ LossWs carve_ws(const aj_loss_cfg &c, int n_tgt, void *base) {
   w.part = cv.take<float>(kFinBlocks * 8);
   w.dhn = cv.take<float>((int64_t)n_tgt * c.d_model);
   w.dg_part = cv.take<float>(aj::rmsnorm_bwd_part_floats(n_tgt, c.d_model));
-  // the dW_vocab GEMM runs on full groups and on the last, narrower one:
-  // their split-K factors (tile counts) differ
-  const size_t sk = std::max(aj::gemm_split_floats((int)gfull, c.d_model, n_tgt),
-                             aj::gemm_split_floats((int)glast, c.d_model, n_tgt));
-  w.splitk = cv.take<float>(sk > 0 ? sk : 1);
-  w.splitk_floats = sk > 0 ? sk : 1;
+  w.splitk_floats = std::max(aj::gemm_partial_floats(gfull, c.d_model),
+                             aj::gemm_partial_floats(n_tgt, c.d_model));
+  w.splitk = cv.take<float>(w.splitk_floats);
   w.bytes = cv.bytes();
   return w;
 }
@@ -709,13 +706,14 @@ int loss_bwd(const aj_loss_cfg &c, const aj_loss_in &in, const void *h, const vo
     g.M = n; g.N = d; g.K = gw; g.A = w.dz; g.lda = gw;
     g.B = (const T *)w_vocab + (int64_t)g0 * d; g.ldb = d; g.b_kmajor = false;
     g.C = w.dhn; g.ldc = d; g.out = aj::OUT_ACCUM_F32;
+    g.partial = w.splitk; g.partial_cap = w.splitk_floats;
     if ((r = aj::gemm<T>(g, st))) return r;
     if (!dwv) continue;   // frozen LM head
     g = aj::Gemm();   // dW_group += dz^T hn
     g.M = gw; g.N = d; g.K = n; g.A = w.dz; g.lda = gw; g.a_kmajor = false;
     g.B = sv.hn; g.ldb = d; g.b_kmajor = false;
     g.C = dwv + (int64_t)g0 * d; g.ldc = d; g.out = aj::OUT_ACCUM_F32;
-    g.split_k = aj::gemm_split_k(g.M, g.N, g.K); g.partial = w.splitk;
+    g.partial = w.splitk;
     g.partial_cap = w.splitk_floats;
     if ((r = aj::gemm<T>(g, st))) return r;
   }

@@ -56,16 +56,15 @@ struct Gemm {
   bool c_f32 = false;          // C element type: float32, else the input type
   int out = OUT_STORE;         // OUT_ACCUM_F32: C (float32) += A B
   const void *R = nullptr;     // optional residual, same type/ld as C: C = A B + R
-  int split_k = 1;             // > 1: partial sums in `partial`, reduced in fixed order
-  float *partial = nullptr;    // split_k * M * N floats (OUT_ACCUM_F32 or c_f32 only)
-  size_t partial_cap = 0;      // floats available at `partial` (checked before any launch)
-  // SwiGLU backward in the epilogue (bfloat16 only, no split-K): the product is
+  float *partial = nullptr;    // scratch for the sums of a split reduction, or null
+  size_t partial_cap = 0;      // floats available there: what does not fit is not split
+  // SwiGLU backward in the epilogue (bfloat16 only): the product is
   // d s (N = F columns); with gate g = gu[m][n] and up u = gu[m][F + n] (row
   // stride ldc = 2F) the epilogue stores d gate = d s u sig(g) (1 + g (1 - sig(g)))
   // at C[m][n] and d up = d s g sig(g) at C[m][F + n]
   const void *swiglu_gu = nullptr;
   bool recompute = false;      // recomputes a forward product: no algorithmic flops
-  // optional second reduction segment, same operand layouts, no split-K:
+  // optional second reduction segment, same operand layouts, never split:
   // C (op) A B + A2 B2 with k in [0, K) and [0, K2)
   const void *A2 = nullptr; int64_t lda2 = 0;
   const void *B2 = nullptr; int64_t ldb2 = 0;
@@ -74,31 +73,32 @@ struct Gemm {
 template <typename T>
 int gemm(const Gemm &g, hipStream_t s);
 
-// Split-K factor for an M x N output over K (K/S >= 4096): with fewer 256x256
-// tiles than CUs, enough splits for ~1.5-2 rounds of 256 workgroups; with
-// more, a split of at most 4 when it fills the last round clearly better
-// (one workgroup per CU: a part-filled round costs a whole one).
+// How the bfloat16 matrix-core kernels run a product: tiles of tile x tile
+// outputs, of which the first `whole` take one workgroup each and each of the
+// rest `split` workgroups over ranges of k_piece, whose sums go to the scratch.
+struct GemmPlan {
+  int tile;             // 256 or 128
+  bool long_k;          // 256: the 4-wave kernel
+  int tiles, whole, split, k_piece;
+};
+GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool whole_only, bool swiglu);
+
+constexpr int kMaxSplit = 16;
+// Scratch for the products of M x N outputs, in floats: every split stays
+// inside min(kMaxSplit * tiles, 512) blocks of 256 x 256.  Not a function of
+// the reduction, and never less for a larger M or N: a caller's buffers sized
+// for its largest pack serve the smaller ones.
+inline size_t gemm_partial_floats(int64_t M, int64_t N) {
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  return (size_t)(tiles * kMaxSplit < 512 ? tiles * kMaxSplit : 512) * 65536;
+}
+// Split factor of the plain kernel for an M x N output over K (K/S >= 4096).
 inline int gemm_split_k(int M, int N, int K) {
   const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  if (K < 8192) return 1;
-  const int kmax = K / 4096 < 16 ? K / 4096 : 16;
-  if (tiles < 240) {
-    const int S = (448 + tiles - 1) / tiles;
-    return S > kmax ? kmax : (S < 1 ? 1 : S);
-  }
-  auto idle = [&](int S) {   // idle fraction of the rounds
-    const long t = (long)tiles * S, slots = (t + 255) / 256 * 256;
-    return (double)(slots - t) / (double)slots;
-  };
-  int best = 1;
-  for (int S = 2; S <= 4 && S <= kmax; ++S)
-    if (idle(S) < idle(best) - 0.08) best = S;
-  return best;
-}
-// Floats of split-K partials gemm() needs for such a GEMM (0 when no split).
-inline size_t gemm_split_floats(int M, int N, int K) {
-  const int S = gemm_split_k(M, N, K);
-  return S > 1 ? (size_t)S * M * N : 0;
+  if (K < 8192 || tiles > 256) return 1;
+  const int kmax = K / 4096 < kMaxSplit ? K / 4096 : kMaxSplit;
+  const int S = 512 / tiles;
+  return S > kmax ? kmax : S;
 }
 
 // ---------------------------------------------------------------- attention

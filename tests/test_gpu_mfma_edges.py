@@ -21,7 +21,10 @@ pytestmark = pytest.mark.gpu
 # every remainder of the four-stage ring), ragged ends; one row to two tiles
 SIZES = [(1, 8, 8, 8), (31, 24, 40, 40), (33, 40, 264, 96), (255, 64, 256, 256), (257, 104, 520, 264),
          (300, 136, 1000, 512), (64, 160, 96, 96), (129, 264, 288, 144), (700, 32, 2056, 2056),
-         (96, 520, 130, 128)]
+         (96, 520, 130, 128),
+         # reductions in pieces: every tile's (few tiles), and those of the tiles
+         # past a full round of 256 (65 x 5 tiles of d hidden)
+         (300, 136, 4104, 4104), (2000, 264, 2600, 2600), (16500, 1032, 2056, 2056)]
 
 
 def _bf(x):
