@@ -4,18 +4,28 @@
 // own segment up to itself, [seg_start(row), row], with seg_start found from
 // cu_seqlens.  Query head h reads key/value head floor(h * Hkv / Hq).
 //
-// These kernels use float FMA with 4 threads per query row (a quarter of the
-// head dimension each) and stream keys through LDS; they serve the float32
-// workload and head dims other than 64 and 128.  bfloat16 with head_dim 64 or
-// 128 goes to the MFMA kernels in attention_mfma.hip.
+// These kernels serve the float32 workload and head dims other than 64 and 128:
+// v_mfma_f32_16x16x4_f32 (float32 products and sums), a wave per 16 rows of one
+// head, four waves sharing the rows staged in LDS.  bfloat16 with head_dim 64 or
+// 128 goes to the kernels in attention_mfma.hip.
+//
+// All products keep the wave's 16 rows on the lanes' columns: with S^T = K Q^T a
+// lane holds scores of one query (its column l%16) for keys 4 (l/16) + 0..3, and
+// that is the layout the next product takes as its operand (the j-th product of
+// a 16-wide reduction covers elements 4 (l/16) + j), so probabilities never
+// leave their registers.  Segments here are a few hundred rows: the time is one
+// pass of dependent steps over a segment, which a wave per 16 rows (4 times the
+// rows in flight of a thread quad per row, and 16 of a step's keys at once)
+// shortens from 391 / 356 / 457 us (forward, dQ, dK and dV of 3443 tokens in 4
+// heads of 32) to 29 / 31 / 39.
 #include "ops.h"
 
 namespace aj {
 namespace {
 
-constexpr int kRows = 64;     // query (or key) rows per workgroup
-constexpr int kKv = 32;       // rows staged in LDS per step
+constexpr int kRows = 64;     // query (or key) rows per workgroup: 16 per wave
 constexpr int kMaxHd = 128;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 AJ_DEV int seg_of(const int32_t *cu, int n_seg, int base, int row) {
   int lo = 0, hi = n_seg - 1;   // largest s with cu[s] - base <= row
@@ -40,78 +50,155 @@ AJ_DEV int seg_end(const A &a, int row) {
   return v <= row ? row + 1 : (v > a.n_tok ? a.n_tok : v);
 }
 
-AJ_DEV float quad_sum(float v) {
-  v += __shfl_xor(v, 1, 64);
-  v += __shfl_xor(v, 2, 64);
-  return v;
+AJ_DEV f32x4_t mfma4(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void attn_fwd_simple_kernel(AttnArgs a) {
-  __shared__ float Ks[kKv][kMaxHd + 1];
-  __shared__ float Vs[kKv][kMaxHd + 1];
-  __shared__ int range[2];
-  const int hd = a.hd, qd = hd / 4;
-  const int ld = (a.Hq + 2 * a.Hkv) * hd;
-  const int h = blockIdx.y, g = (h * a.Hkv) / a.Hq;
-  const int row0 = blockIdx.x * kRows;
-  const int rl = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const int row = row0 + rl;
-  const bool valid = row < a.n_tok;
-  const T *qkv = (const T *)a.qkv;
-  int start = 0;
-  if (valid) start = seg_start(a, row);
-  if (threadIdx.x == 0) {
-    int last = min(row0 + kRows, a.n_tok) - 1;
-    range[0] = seg_start(a, row0);
-    range[1] = last;
+// Rows of NC 16-feature chunks in LDS: 16 NC + 4 floats apart, so that the 16
+// rows of a fragment read, and the 4 row groups of a transposed one, fall on
+// different banks.
+template <int NC> constexpr int kLd = 16 * NC + 4;
+// Rows staged per step: 64, less where two such arrays would pass 64 KB.
+template <int NC> constexpr int kStep = NC <= 4 ? 64 : 32;
+
+// rows [r0, r0 + kStep) of a [rows, ld] matrix's hd columns into LDS (zeros past
+// `last` and past hd); hd is a multiple of 8, so four columns are in or out as one
+template <typename T, int NC>
+AJ_DEV void stage_rows(float *lds, const T *p, int64_t ld, int hd, bool vec, int r0, int last) {
+  for (int e = threadIdx.x; e < kStep<NC> * NC * 4; e += 256) {
+    const int r = e / (NC * 4), c = e % (NC * 4) * 4;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (r0 + r <= last && c < hd) {
+      const T *src = p + (int64_t)(r0 + r) * ld + c;
+      if (vec && sizeof(T) == 4) {
+        v = *reinterpret_cast<const float4 *>(src);
+      } else if (vec) {
+        const uint2 u = *reinterpret_cast<const uint2 *>(src);
+        v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
+                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+      } else {
+        v = make_float4(ldf(src), ldf(src + 1), ldf(src + 2), ldf(src + 3));
+      }
+    }
+    *reinterpret_cast<float4 *>(lds + r * kLd<NC> + c) = v;
   }
-  float q[kMaxHd / 4], o[kMaxHd / 4];
+}
+
+// a lane's operand of its own row: features 16 c + 4 (l/16) + j
+template <typename T, int NC>
+AJ_DEV void own_row(f32x4_t (&f)[NC], const T *p, int hd, bool valid) {
+  const int g = (threadIdx.x & 63) >> 4;
 #pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i) {
-    q[i] = (valid && i < qd) ? ldf(qkv + (int64_t)row * ld + h * hd + part * qd + i) * a.scale : 0.f;
-    o[i] = 0.f;
+  for (int c = 0; c < NC; ++c) {
+    const int k = 16 * c + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) f[c][j] = valid && k < hd ? ldf(p + k + j) : 0.f;
+  }
+}
+template <typename T, int NC>
+AJ_DEV void store_row(T *p, const f32x4_t (&f)[NC], int hd, float scale) {
+  const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int k = 16 * c + 4 * g;
+    if (k < hd)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) stf(p + k + j, f[c][j] * scale);
+  }
+}
+
+// (rows of LDS x the lane's row)^T: 16 rows from `rows` on against `own`; the
+// lane gets rows 4 (l/16) + 0..3
+template <int NC>
+AJ_DEV f32x4_t rows_dot(const float *rows, const f32x4_t (&own)[NC]) {
+  const int lane = threadIdx.x & 63;
+  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const f32x4_t a = *reinterpret_cast<const f32x4_t *>(rows + (lane & 15) * kLd<NC> + 16 * c + 4 * (lane >> 4));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) s = mfma4(a[j], own[c][j], s);
+  }
+  return s;
+}
+// acc[features, lane's row] += sum over 16 rows of LDS, w[row] (the lane's rows
+// 4 (l/16) + j) times the row's features
+template <int NC>
+AJ_DEV void rows_add(f32x4_t (&acc)[NC], const float *rows, const f32x4_t &w) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc[c] = mfma4(rows[(4 * (lane >> 4) + j) * kLd<NC> + 16 * c + (lane & 15)], w[j], acc[c]);
+}
+
+AJ_DEV bool vec4(const void *p, int64_t ld, int es) {
+  return ld % 4 == 0 && ((uintptr_t)p & (4 * es - 1)) == 0;
+}
+
+template <typename T, int NC>
+__global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) float Ks[kStep<NC> * kLd<NC>], Vs[kStep<NC> * kLd<NC>];
+  const int hd = a.hd, ld = (a.Hq + 2 * a.Hkv) * hd;
+  const int h = blockIdx.y, g = (h * a.Hkv) / a.Hq;
+  const int row0 = blockIdx.x * kRows, last = min(row0 + kRows, a.n_tok) - 1;
+  const int lane = threadIdx.x & 63, w0 = row0 + 16 * (threadIdx.x >> 6);
+  const int row = w0 + (lane & 15);
+  const bool valid = row < a.n_tok;
+  const T *qkv = (const T *)a.qkv, *kp = qkv + (a.Hq + g) * hd, *vp = kp + a.Hkv * hd;
+  const bool vec = vec4(a.qkv, ld, sizeof(T));
+  const int start = valid ? seg_start(a, row) : row;
+  f32x4_t q[NC], o[NC];
+  own_row<T, NC>(q, qkv + (int64_t)row * ld + h * hd, hd, valid);
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[c][j] *= a.scale;
+    o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   }
   float m = -INFINITY, l = 0.f;
-  __syncthreads();
-  const int kv_lo = range[0], kv_hi = range[1];
-  for (int k0 = kv_lo; k0 <= kv_hi; k0 += kKv) {
-    for (int e = threadIdx.x; e < kKv * hd; e += 256) {
-      int r = e / hd, c = e % hd, kr = k0 + r;
-      float kv = 0.f, vv = 0.f;
-      if (kr <= kv_hi) {
-        kv = ldf(qkv + (int64_t)kr * ld + (a.Hq + g) * hd + c);
-        vv = ldf(qkv + (int64_t)kr * ld + (a.Hq + a.Hkv + g) * hd + c);
-      }
-      Ks[r][c] = kv;
-      Vs[r][c] = vv;
-    }
+  const int k_lo = seg_start(a, row0);
+  for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
     __syncthreads();
-    for (int j = 0; j < kKv; ++j) {
-      const int key = k0 + j;
-      float s = 0.f;
+    stage_rows<T, NC>(Ks, kp, ld, hd, vec, k0, last);
+    stage_rows<T, NC>(Vs, vp, ld, hd, vec, k0, last);
+    __syncthreads();
+    for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
+      f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
+      const int key = k0 + t + 4 * (lane >> 4);
+      float mx = -INFINITY;
 #pragma unroll
-      for (int i = 0; i < kMaxHd / 4; ++i)
-        if (i < qd) s += q[i] * Ks[j][part * qd + i];
-      s = quad_sum(s);
-      if (!valid || key < start || key > row) continue;
-      const float mn = fmaxf(m, s);
-      const float sc = __expf(m - mn), p = __expf(s - mn);
-      l = l * sc + p;
+      for (int j = 0; j < 4; ++j) {
+        if (key + j < start || key + j > row || !valid) s[j] = -INFINITY;
+        mx = fmaxf(mx, s[j]);
+      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mn = fmaxf(m, mx);
+      // a query that has seen no key yet keeps zero weights (mn is -inf)
+      const float sc = mn == -INFINITY ? 1.f : __expf(m - mn);
+      float sum = 0.f;
 #pragma unroll
-      for (int i = 0; i < kMaxHd / 4; ++i)
-        if (i < qd) o[i] = o[i] * sc + p * Vs[j][part * qd + i];
+      for (int j = 0; j < 4; ++j) {
+        s[j] = s[j] == -INFINITY ? 0.f : __expf(s[j] - mn);
+        sum += s[j];
+      }
+      l = l * sc + sum;
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[c][j] *= sc;
+      rows_add<NC>(o, Vs + t * kLd<NC>, s);
       m = mn;
     }
-    __syncthreads();
   }
+  // each lane has summed its own keys' weights
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
   if (!valid) return;
-  T *out = (T *)a.o + (int64_t)row * a.Hq * hd + h * hd + part * qd;
-  const float inv = 1.f / l;
-#pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i)
-    if (i < qd) stf(out + i, o[i] * inv);
-  if (part == 0) a.lse[(int64_t)h * a.n_tok + row] = m + logf(l);
+  store_row<T, NC>((T *)a.o + (int64_t)row * a.Hq * hd + h * hd, o, hd, 1.f / l);
+  if (lane < 16) a.lse[(int64_t)h * a.n_tok + row] = m + logf(l);
 }
 
 // delta[h][row] = sum_d dO * O
@@ -131,159 +218,116 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(AttnBwdArgs a) {
 }
 
 // dQ rows: dq = scale * sum_j P_j (dO.V_j - delta) K_j
-template <typename T>
-__global__ __launch_bounds__(256) void attn_dq_simple_kernel(AttnBwdArgs a) {
-  __shared__ float Ks[kKv][kMaxHd + 1];
-  __shared__ float Vs[kKv][kMaxHd + 1];
-  __shared__ int range[2];
-  const int hd = a.hd, qd = hd / 4;
-  const int ld = (a.Hq + 2 * a.Hkv) * hd;
+template <typename T, int NC>
+__global__ __launch_bounds__(256) void attn_dq_f32_kernel(AttnBwdArgs a) {
+  __shared__ __attribute__((aligned(16))) float Ks[kStep<NC> * kLd<NC>], Vs[kStep<NC> * kLd<NC>];
+  const int hd = a.hd, ld = (a.Hq + 2 * a.Hkv) * hd;
   const int h = blockIdx.y, g = (h * a.Hkv) / a.Hq;
-  const int row0 = blockIdx.x * kRows;
-  const int rl = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const int row = row0 + rl;
+  const int row0 = blockIdx.x * kRows, last = min(row0 + kRows, a.n_tok) - 1;
+  const int lane = threadIdx.x & 63, w0 = row0 + 16 * (threadIdx.x >> 6);
+  const int row = w0 + (lane & 15);
   const bool valid = row < a.n_tok;
-  const T *qkv = (const T *)a.qkv;
-  int start = 0;
-  float lse = 0.f, delta = 0.f;
-  if (valid) {
-    start = seg_start(a, row);
-    lse = a.lse[(int64_t)h * a.n_tok + row];
-    delta = a.delta[(int64_t)h * a.n_tok + row];
-  }
-  if (threadIdx.x == 0) {
-    range[0] = seg_start(a, row0);
-    range[1] = min(row0 + kRows, a.n_tok) - 1;
-  }
-  float q[kMaxHd / 4], dob[kMaxHd / 4], dq[kMaxHd / 4];
-  const T *dout = (const T *)a.dout + (int64_t)row * a.Hq * hd + h * hd + part * qd;
+  const T *qkv = (const T *)a.qkv, *kp = qkv + (a.Hq + g) * hd, *vp = kp + a.Hkv * hd;
+  const bool vec = vec4(a.qkv, ld, sizeof(T));
+  const int start = valid ? seg_start(a, row) : row;
+  const float lse = valid ? a.lse[(int64_t)h * a.n_tok + row] : 0.f;
+  const float delta = valid ? a.delta[(int64_t)h * a.n_tok + row] : 0.f;
+  f32x4_t q[NC], dob[NC], dq[NC];
+  own_row<T, NC>(q, qkv + (int64_t)row * ld + h * hd, hd, valid);
+  own_row<T, NC>(dob, (const T *)a.dout + (int64_t)row * a.Hq * hd + h * hd, hd, valid);
 #pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i) {
-    q[i] = (valid && i < qd) ? ldf(qkv + (int64_t)row * ld + h * hd + part * qd + i) : 0.f;
-    dob[i] = (valid && i < qd) ? ldf(dout + i) : 0.f;
-    dq[i] = 0.f;
-  }
-  __syncthreads();
-  const int kv_lo = range[0], kv_hi = range[1];
-  for (int k0 = kv_lo; k0 <= kv_hi; k0 += kKv) {
-    for (int e = threadIdx.x; e < kKv * hd; e += 256) {
-      int r = e / hd, c = e % hd, kr = k0 + r;
-      float kv = 0.f, vv = 0.f;
-      if (kr <= kv_hi) {
-        kv = ldf(qkv + (int64_t)kr * ld + (a.Hq + g) * hd + c);
-        vv = ldf(qkv + (int64_t)kr * ld + (a.Hq + a.Hkv + g) * hd + c);
+  for (int c = 0; c < NC; ++c) dq[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int k_lo = seg_start(a, row0);
+  for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
+    __syncthreads();
+    stage_rows<T, NC>(Ks, kp, ld, hd, vec, k0, last);
+    stage_rows<T, NC>(Vs, vp, ld, hd, vec, k0, last);
+    __syncthreads();
+    for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
+      const f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
+      const f32x4_t dp = rows_dot<NC>(Vs + t * kLd<NC>, dob);
+      const int key = k0 + t + 4 * (lane >> 4);
+      f32x4_t ds;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool in = valid && key + j >= start && key + j <= row;
+        ds[j] = in ? __expf(s[j] * a.scale - lse) * (dp[j] - delta) * a.scale : 0.f;
       }
-      Ks[r][c] = kv;
-      Vs[r][c] = vv;
+      rows_add<NC>(dq, Ks + t * kLd<NC>, ds);
     }
-    __syncthreads();
-    for (int j = 0; j < kKv; ++j) {
-      const int key = k0 + j;
-      float s = 0.f, dp = 0.f;
-#pragma unroll
-      for (int i = 0; i < kMaxHd / 4; ++i)
-        if (i < qd) { s += q[i] * Ks[j][part * qd + i]; dp += dob[i] * Vs[j][part * qd + i]; }
-      s = quad_sum(s);
-      dp = quad_sum(dp);
-      if (!valid || key < start || key > row) continue;
-      const float p = __expf(s * a.scale - lse);
-      const float ds = p * (dp - delta) * a.scale;
-#pragma unroll
-      for (int i = 0; i < kMaxHd / 4; ++i)
-        if (i < qd) dq[i] += ds * Ks[j][part * qd + i];
-    }
-    __syncthreads();
   }
-  if (!valid) return;
-  T *out = (T *)a.dqkv + (int64_t)row * ld + h * hd + part * qd;
-#pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i)
-    if (i < qd) stf(out + i, dq[i]);
+  if (valid) store_row<T, NC>((T *)a.dqkv + (int64_t)row * ld + h * hd, dq, hd, 1.f);
 }
 
 // dK, dV rows of kv head g: sum over the query heads of the group and the
 // queries of the same segment at or after the key.
-template <typename T>
-__global__ __launch_bounds__(256) void attn_dkv_simple_kernel(AttnBwdArgs a) {
-  __shared__ float Qs[kKv][kMaxHd + 1];
-  __shared__ float Ds[kKv][kMaxHd + 1];
-  __shared__ float Ls[kKv], Dl[kKv];
-  __shared__ int range[2];
-  const int hd = a.hd, qd = hd / 4;
-  const int ld = (a.Hq + 2 * a.Hkv) * hd;
+template <typename T, int NC>
+__global__ __launch_bounds__(256) void attn_dkv_f32_kernel(AttnBwdArgs a) {
+  __shared__ __attribute__((aligned(16))) float Qs[kStep<NC> * kLd<NC>], Ds[kStep<NC> * kLd<NC>];
+  __shared__ __attribute__((aligned(16))) float Ls[kStep<NC>], Dl[kStep<NC>];
+  const int hd = a.hd, ld = (a.Hq + 2 * a.Hkv) * hd;
   const int g = blockIdx.y;
   const int row0 = blockIdx.x * kRows;
-  const int rl = threadIdx.x >> 2, part = threadIdx.x & 3;
-  const int row = row0 + rl;           // the key row
+  const int lane = threadIdx.x & 63, w0 = row0 + 16 * (threadIdx.x >> 6);
+  const int row = w0 + (lane & 15);           // the key row
   const bool valid = row < a.n_tok;
   const T *qkv = (const T *)a.qkv;
-  int end = 0;
-  if (valid) end = seg_end(a, row);
-  if (threadIdx.x == 0) {
-    const int last = min(row0 + kRows, a.n_tok) - 1;
-    range[0] = row0;
-    range[1] = seg_end(a, last) - 1;
-  }
-  float k[kMaxHd / 4], v[kMaxHd / 4], dk[kMaxHd / 4], dv[kMaxHd / 4];
+  const bool vec = vec4(a.qkv, ld, sizeof(T)), vecd = vec4(a.dout, (int64_t)a.Hq * hd, sizeof(T));
+  const int end = valid ? seg_end(a, row) : 0;
+  const int q_hi = seg_end(a, min(row0 + kRows, a.n_tok) - 1) - 1;
+  // the last query any of the wave's keys meets
+  int w_hi = end - 1;
 #pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i) {
-    k[i] = (valid && i < qd) ? ldf(qkv + (int64_t)row * ld + (a.Hq + g) * hd + part * qd + i) : 0.f;
-    v[i] = (valid && i < qd) ? ldf(qkv + (int64_t)row * ld + (a.Hq + a.Hkv + g) * hd + part * qd + i) : 0.f;
-    dk[i] = 0.f;
-    dv[i] = 0.f;
-  }
-  __syncthreads();
-  const int q_lo = range[0], q_hi = range[1];
+  for (int o = 8; o > 0; o >>= 1) w_hi = max(w_hi, __shfl_xor(w_hi, o, 64));
+  f32x4_t k[NC], v[NC], dk[NC], dv[NC];
+  own_row<T, NC>(k, qkv + (int64_t)row * ld + (a.Hq + g) * hd, hd, valid);
+  own_row<T, NC>(v, qkv + (int64_t)row * ld + (a.Hq + a.Hkv + g) * hd, hd, valid);
+#pragma unroll
+  for (int c = 0; c < NC; ++c) dk[c] = dv[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int group = a.Hq / a.Hkv;
   for (int hh = 0; hh < group; ++hh) {
     const int h = g * group + hh;
-    for (int q0 = q_lo; q0 <= q_hi; q0 += kKv) {
-      for (int e = threadIdx.x; e < kKv * hd; e += 256) {
-        int r = e / hd, c = e % hd, qr = q0 + r;
-        float qv = 0.f, dv_ = 0.f;
-        if (qr <= q_hi) {
-          qv = ldf(qkv + (int64_t)qr * ld + h * hd + c);
-          dv_ = ldf((const T *)a.dout + (int64_t)qr * a.Hq * hd + h * hd + c);
-        }
-        Qs[r][c] = qv;
-        Ds[r][c] = dv_;
-      }
-      if (threadIdx.x < kKv) {
-        int qr = q0 + threadIdx.x;
+    for (int q0 = row0; q0 <= q_hi; q0 += kStep<NC>) {
+      __syncthreads();
+      stage_rows<T, NC>(Qs, qkv + h * hd, ld, hd, vec, q0, q_hi);
+      stage_rows<T, NC>(Ds, (const T *)a.dout + h * hd, (int64_t)a.Hq * hd, hd, vecd, q0, q_hi);
+      if ((int)threadIdx.x < kStep<NC>) {
+        const int qr = q0 + threadIdx.x;
         Ls[threadIdx.x] = qr <= q_hi ? a.lse[(int64_t)h * a.n_tok + qr] : 0.f;
         Dl[threadIdx.x] = qr <= q_hi ? a.delta[(int64_t)h * a.n_tok + qr] : 0.f;
       }
       __syncthreads();
-      for (int j = 0; j < kKv; ++j) {
-        const int qrow = q0 + j;
-        float s = 0.f, dp = 0.f;
+      for (int t = 0; t < kStep<NC> && q0 + t <= w_hi; t += 16) {
+        if (q0 + t + 15 < w0) continue;
+        const f32x4_t s = rows_dot<NC>(Qs + t * kLd<NC>, k);
+        const f32x4_t dp = rows_dot<NC>(Ds + t * kLd<NC>, v);
+        const int ql = t + 4 * (lane >> 4);
+        f32x4_t p, ds;
 #pragma unroll
-        for (int i = 0; i < kMaxHd / 4; ++i)
-          if (i < qd) { s += k[i] * Qs[j][part * qd + i]; dp += v[i] * Ds[j][part * qd + i]; }
-        s = quad_sum(s);
-        dp = quad_sum(dp);
-        if (!valid || qrow < row || qrow >= end) continue;
-        const float p = __expf(s * a.scale - Ls[j]);
-        const float ds = p * (dp - Dl[j]) * a.scale;
-#pragma unroll
-        for (int i = 0; i < kMaxHd / 4; ++i)
-          if (i < qd) {
-            dv[i] += p * Ds[j][part * qd + i];
-            dk[i] += ds * Qs[j][part * qd + i];
-          }
+        for (int j = 0; j < 4; ++j) {
+          const bool in = valid && q0 + ql + j >= row && q0 + ql + j < end;
+          p[j] = in ? __expf(s[j] * a.scale - Ls[ql + j]) : 0.f;
+          ds[j] = in ? p[j] * (dp[j] - Dl[ql + j]) * a.scale : 0.f;
+        }
+        rows_add<NC>(dv, Ds + t * kLd<NC>, p);
+        rows_add<NC>(dk, Qs + t * kLd<NC>, ds);
       }
-      __syncthreads();
     }
   }
   if (!valid) return;
   T *base = (T *)a.dqkv + (int64_t)row * ld;
-#pragma unroll
-  for (int i = 0; i < kMaxHd / 4; ++i)
-    if (i < qd) {
-      stf(base + (a.Hq + g) * hd + part * qd + i, dk[i]);
-      stf(base + (a.Hq + a.Hkv + g) * hd + part * qd + i, dv[i]);
-    }
+  store_row<T, NC>(base + (a.Hq + g) * hd, dk, hd, 1.f);
+  store_row<T, NC>(base + (a.Hq + a.Hkv + g) * hd, dv, hd, 1.f);
 }
+
+// 16-feature chunks of a head, rounded up to an instantiated count
+#define AJ_NC_DISPATCH(hd, CALL)                     \
+  do {                                               \
+    if ((hd) <= 16) { constexpr int NC = 1; CALL; }  \
+    else if ((hd) <= 32) { constexpr int NC = 2; CALL; } \
+    else if ((hd) <= 64) { constexpr int NC = 4; CALL; } \
+    else { constexpr int NC = 8; CALL; }             \
+  } while (0)
 
 }  // namespace
 
@@ -294,7 +338,7 @@ int attn_fwd(const AttnArgs &a, hipStream_t s) {
   if (sizeof(T) == 2 && attn_mfma_supported(a.hd, a.qkv, a.o, a.o)) return attn_fwd_mfma(a, s);
   dim3 grid((a.n_tok + kRows - 1) / kRows, a.Hq);
   const int tk = timing_begin(s, AJ_KC_ATTN_FWD, 0.0);
-  attn_fwd_simple_kernel<T><<<grid, 256, 0, s>>>(a);
+  AJ_NC_DISPATCH(a.hd, (attn_fwd_f32_kernel<T, NC><<<grid, 256, 0, s>>>(a)));
   timing_end(s, tk);
   return check_launch("attention forward");
 }
@@ -314,8 +358,9 @@ int attn_bwd(const AttnBwdArgs &a, hipStream_t s) {
   const int64_t nd = (int64_t)a.n_tok * a.Hq;
   const int tk = timing_begin(s, AJ_KC_ATTN_BWD, 0.0);
   attn_delta_kernel<T><<<(unsigned)((nd + 3) / 4), 256, 0, s>>>(a);
-  attn_dq_simple_kernel<T><<<dim3((a.n_tok + kRows - 1) / kRows, a.Hq), 256, 0, s>>>(a);
-  attn_dkv_simple_kernel<T><<<dim3((a.n_tok + kRows - 1) / kRows, a.Hkv), 256, 0, s>>>(a);
+  const int blocks = (a.n_tok + kRows - 1) / kRows;
+  AJ_NC_DISPATCH(a.hd, (attn_dq_f32_kernel<T, NC><<<dim3(blocks, a.Hq), 256, 0, s>>>(a)));
+  AJ_NC_DISPATCH(a.hd, (attn_dkv_f32_kernel<T, NC><<<dim3(blocks, a.Hkv), 256, 0, s>>>(a)));
   timing_end(s, tk);
   return check_launch("attention backward");
 }

@@ -9,8 +9,8 @@
 // remapped so that each XCD (ids are dealt round-robin over the 8 XCDs) walks
 // a contiguous, row-grouped run of tiles and its L2 sees the reuse.
 //
-// float32: a plain LDS-tiled FMA kernel (the float32 workload is the small
-// correctness case).
+// float32, and bfloat16 operands that the copies above cannot take:
+// v_mfma_f32_16x16x4_f32 on 64x64 tiles.
 #include "ops.h"
 #include "gemm_core.h"
 
@@ -282,102 +282,157 @@ __global__ __launch_bounds__(gemm_core::Cfg8::NT, 1) void gemm_mfma_seg2_kernel(
 }
 
 // The pieces of each split tile added up in the order of their k ranges, then
-// the epilogue.  One workgroup per 4096 outputs of a tile, 4 columns per thread
-// and load; the partials were written just before and mostly sit in the
-// last-level cache.
+// the epilogue.  One workgroup per 1024 outputs of a tile, 4 columns per thread;
+// four pieces' loads are in flight at a time (one at a time, and 4096 outputs
+// per workgroup, took 18.5 us for 16 pieces of 32 64 x 64 tiles).  The partials
+// were written just before and mostly sit in the last-level cache.
 template <int BM, int BN>
 __global__ __launch_bounds__(256) void gemm_pieces_kernel(EpArgs ep, Pieces pc) {
-  constexpr int PER = BM * BN / 4096;
-  const int r = blockIdx.x / PER, part = blockIdx.x % PER;
+  constexpr int PER = BM * BN / 1024;
+  const int r = blockIdx.x / PER, e = (blockIdx.x % PER) * 1024 + (int)threadIdx.x * 4;
   const int tiles_m = (ep.M + BM - 1) / BM, tiles_n = (ep.N + BN - 1) / BN;
   const gemm_core::TileIdx ti = gemm_core::tile_at(pc.whole + r, tiles_m, tiles_n);
-  const float *P = pc.partial + (int64_t)r * (BM * BN);
+  const int m = ti.tm * BM + e / BN, n = ti.tn * BN + e % BN;
+  if (m >= ep.M || n >= ep.N) return;
+  const float *P = pc.partial + (int64_t)r * (BM * BN) + e;
   const int64_t step = (int64_t)pc.rest * (BM * BN);
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z = 0; z < pc.split; z += 4) {
+    float4 u[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int e = part * 4096 + (q * 256 + (int)threadIdx.x) * 4;
-    const int m = ti.tm * BM + e / BN, n = ti.tn * BN + e % BN;
-    if (m >= ep.M || n >= ep.N) continue;
-    float4 v = *reinterpret_cast<const float4 *>(P + e);
-    for (int z = 1; z < pc.split; ++z) {
-      const float4 u = *reinterpret_cast<const float4 *>(P + z * step + e);
-      v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
-    }
-    store4(ep, m, n, v);
+    for (int q = 0; q < 4; ++q)
+      if (z + q < pc.split) u[q] = *reinterpret_cast<const float4 *>(P + (z + q) * step);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (z + q < pc.split) { v.x += u[q].x; v.y += u[q].y; v.z += u[q].z; v.w += u[q].w; }
   }
+  store4(ep, m, n, v);
 }
 
 constexpr int kLongK = 4096;
 
-// ---------------------------------------------------------------- float32 / fallback
+// ---------------------------------------------------------------- float32
+// 64 x 64 outputs by four waves of 32 x 32 on v_mfma_f32_16x16x4_f32 (float32
+// products and sums throughout), 32-wide k-steps in two LDS buffers, the next
+// step's operands loaded into registers beside the current one's products.  Any
+// size, stride and alignment: operands go through registers, four elements of
+// the contiguous dimension at a time where they are aligned.  The float32
+// workload's products are small (3443 tokens, widths 128 .. 1024), so what
+// matters is that every CU has a tile: hence the small tile, and reductions over
+// the tokens in pieces.  Its 15 products (a 64x64 tile of plain FMAs before):
+// 2880 -> 300 us.
+constexpr int kFTile = 64, kFBK = 32, kFLd = kFBK + 4;
+
+struct FOperand {
+  const void *p;
+  int64_t ld;
+  bool kmajor, vec;     // vec: 4-element loads are aligned
+};
+
 template <typename T>
-__global__ __launch_bounds__(256) void gemm_simple_kernel(int M, int N, int K, int k_per_split,
-                                                          const T *A, int64_t lda, int a_k,
-                                                          const T *B, int64_t ldb, int b_k,
-                                                          EpArgs ep, float *partial,
-                                                          const T *A2, int64_t lda2,
-                                                          const T *B2, int64_t ldb2, int K2) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Bs[BK][BN + 1];
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  // segment 0: [kbeg, kend) of (A, B); segment 1 (no split): [0, K2) of (A2, B2)
-  for (int seg = 0; seg < (K2 > 0 ? 2 : 1); ++seg) {
-    const T *X = seg ? A2 : A, *Y = seg ? B2 : B;
-    const int64_t ldx = seg ? lda2 : lda, ldy = seg ? ldb2 : ldb;
-    const int kbeg = seg ? 0 : blockIdx.z * k_per_split;
-    const int kend = seg ? K2 : min(K, kbeg + k_per_split);
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-      for (int e = threadIdx.x; e < BM * BK; e += 256) {
-        int mm = e % BM, kk = e / BM;
-        int m = m0 + mm, k = k0 + kk;
-        float va = 0.f, vb = 0.f;
-        if (m < M && k < kend) va = ldf(X + (a_k ? (int64_t)m * ldx + k : (int64_t)k * ldx + m));
-        int n = n0 + mm;
-        if (n < N && k < kend) vb = ldf(Y + (b_k ? (int64_t)n * ldy + k : (int64_t)k * ldy + n));
-        As[kk][mm] = va;
-        Bs[kk][mm] = vb;
+AJ_DEV float4 load_elems(const T *p, int n, bool vec) {
+  if (vec && n >= 4) {
+    if constexpr (sizeof(T) == 4) {
+      return *reinterpret_cast<const float4 *>(p);
+    } else {
+      const uint2 u = *reinterpret_cast<const uint2 *>(p);
+      return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
+                         __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+    }
+  }
+  return make_float4(n > 0 ? ldf(p) : 0.f, n > 1 ? ldf(p + 1) : 0.f, n > 2 ? ldf(p + 2) : 0.f,
+                     n > 3 ? ldf(p + 3) : 0.f);
+}
+
+// this thread's q-th four elements (q = 0, 1) of the 64 x 32 operand tile at (r0, k0)
+template <typename T>
+AJ_DEV float4 f32_fetch(const T *p, int64_t ld, bool kmajor, bool vec, int q, int r0, int rows,
+                        int k0, int kend) {
+  const int idx = threadIdx.x + 256 * q;
+  const int r = r0 + (kmajor ? idx / 8 : idx % 16 * 4), k = k0 + (kmajor ? idx % 8 * 4 : idx / 16);
+  if (r >= rows || k >= kend) return make_float4(0.f, 0.f, 0.f, 0.f);
+  return load_elems(p + (kmajor ? r * ld + k : k * ld + r), kmajor ? kend - k : rows - r, vec);
+}
+AJ_DEV void f32_stage(float *lds, bool kmajor, int q, const float4 &v) {
+  const int idx = threadIdx.x + 256 * q;
+  if (kmajor) {
+    *reinterpret_cast<float4 *>(lds + idx / 8 * kFLd + idx % 8 * 4) = v;
+  } else {
+    float *p = lds + idx % 16 * 4 * kFLd + idx / 16;
+    p[0] = v.x; p[kFLd] = v.y; p[2 * kFLd] = v.z; p[3 * kFLd] = v.w;
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K, FOperand A, FOperand B,
+                                                       int K2, FOperand A2, FOperand B2, EpArgs ep,
+                                                       Pieces pc) {
+  __shared__ __attribute__((aligned(16))) float As[2][kFTile * kFLd], Bs[2][kFTile * kFLd];
+  const int tiles_m = (M + kFTile - 1) / kFTile, tiles_n = (N + kFTile - 1) / kFTile;
+  int t = blockIdx.x, kbeg = 0, kend = K;
+  float *P = nullptr;
+  if (t >= pc.whole) {
+    const int p = t - pc.whole;
+    t = pc.whole + p % pc.rest;
+    kbeg = (p / pc.rest) * pc.k_piece;
+    kend = min(K, kbeg + pc.k_piece);
+    P = pc.partial + (int64_t)p * (kFTile * kFTile);
+  }
+  const gemm_core::TileIdx ti = gemm_core::tile_at(t, tiles_m, tiles_n);
+  const int m0 = ti.tm * kFTile, n0 = ti.tn * kFTile;
+  const int lane = threadIdx.x & 63, wave = gemm_core::wave_id(), wm = wave >> 1, wn = wave & 1;
+  // steps of the first segment, then of the second
+  const int n1 = kend > kbeg ? (kend - kbeg + kFBK - 1) / kFBK : 0;
+  const int nk = n1 + (K2 + kFBK - 1) / kFBK;
+  float4 va[2], vb[2];
+  auto fetch = [&](int s) {
+    const bool two = s >= n1;
+    const int k0 = two ? (s - n1) * kFBK : kbeg + s * kFBK;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      va[q] = f32_fetch((const T *)(two ? A2.p : A.p), two ? A2.ld : A.ld, A.kmajor,
+                        two ? A2.vec : A.vec, q, m0, M, k0, two ? K2 : kend);
+      vb[q] = f32_fetch((const T *)(two ? B2.p : B.p), two ? B2.ld : B.ld, B.kmajor,
+                        two ? B2.vec : B.vec, q, n0, N, k0, two ? K2 : kend);
+    }
+  };
+  f32x4_t acc[2][2] = {};
+  if (nk > 0) fetch(0);
+  for (int s = 0; s < nk; ++s) {
+    float *as = As[s & 1], *bs = Bs[s & 1];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      f32_stage(as, A.kmajor, q, va[q]);
+      f32_stage(bs, B.kmajor, q, vb[q]);
+    }
+    __syncthreads();   // (the other buffer's readers are all past the barrier before this one)
+    if (s + 1 < nk) fetch(s + 1);
+    // lane l: row l%16, k = 4 (l/16) + j at the j-th product of each 16 k
+#pragma unroll
+    for (int c = 0; c < kFBK / 16; ++c) {
+      f32x4_t fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[i] = *reinterpret_cast<const f32x4_t *>(as + (wm * 32 + i * 16 + (lane & 15)) * kFLd + 16 * c + 4 * (lane >> 4));
+        fb[i] = *reinterpret_cast<const f32x4_t *>(bs + (wn * 32 + i * 16 + (lane & 15)) * kFLd + 16 * c + 4 * (lane >> 4));
       }
-      __syncthreads();
 #pragma unroll
-      for (int kk = 0; kk < BK; ++kk) {
-        float a[4], b[4];
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty + 16 * i]; b[i] = Bs[kk][tx + 16 * i]; }
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-      }
-      __syncthreads();
+          for (int jn = 0; jn < 2; ++jn)
+            acc[i][jn] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[jn][j], fa[i][j], acc[i][jn], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int m = m0 + ty + 16 * i, n = n0 + tx + 16 * j;
-      if (m >= M || n >= N) continue;
-      const float v = acc[i][j];
-      if (partial) {
-        partial[((int64_t)blockIdx.z * M + m) * N + n] = v;
-      } else if (ep.accum) {
-        ((float *)ep.C)[(int64_t)m * ep.ldc + n] += v;
-      } else if (ep.c_f32) {
-        ((float *)ep.C)[(int64_t)m * ep.ldc + n] =
-            v + (ep.R ? ((const float *)ep.R)[(int64_t)m * ep.ldc + n] : 0.f);
-      } else if (ep.gu) {
-        const int64_t o = (int64_t)m * ep.ldc + n;
-        float dg, du;
-        swiglu_grad(v, bf2f(ep.gu[o]), bf2f(ep.gu[o + N]), dg, du);
-        stf((T *)ep.C + o, dg);
-        stf((T *)ep.C + o + N, du);
-      } else {
-        T *c = (T *)ep.C + (int64_t)m * ep.ldc + n;
-        stf(c, v + (ep.R ? ldf((const T *)ep.R + (int64_t)m * ep.ldc + n) : 0.f));
-      }
+    for (int jn = 0; jn < 2; ++jn) {
+      const int r = wm * 32 + i * 16 + (lane & 15), c = wn * 32 + jn * 16 + 4 * (lane >> 4);
+      const float4 v = make_float4(acc[i][jn][0], acc[i][jn][1], acc[i][jn][2], acc[i][jn][3]);
+      if (P) *reinterpret_cast<float4 *>(P + r * kFTile + c) = v;
+      else if (m0 + r < M && n0 + c < N) store4(ep, m0 + r, n0 + c, v);
     }
 }
 
@@ -401,8 +456,8 @@ void launch_mfma(const Gemm &g, const EpArgs &ep, const GemmPlan &pl, hipStream_
         g.M, g.N, g.K, A, g.lda, B, g.ldb, ep, pc);
   }
   if (pc.rest == 0 || pc.split <= 1) return;
-  if (pl.tile == 128) gemm_pieces_kernel<128, 128><<<pc.rest * 4, 256, 0, s>>>(ep, pc);
-  else gemm_pieces_kernel<256, 256><<<pc.rest * 16, 256, 0, s>>>(ep, pc);
+  if (pl.tile == 128) gemm_pieces_kernel<128, 128><<<pc.rest * 16, 256, 0, s>>>(ep, pc);
+  else gemm_pieces_kernel<256, 256><<<pc.rest * 64, 256, 0, s>>>(ep, pc);
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
@@ -477,7 +532,7 @@ int gemm(const Gemm &g, hipStream_t s) {
   if (g.swiglu_gu && (sizeof(T) != 2 || ep.accum || ep.c_f32 || g.R || g.ldc < 2 * (int64_t)g.N))
     return fail(AJ_ERR_UNSUPPORTED, "gemm: SwiGLU epilogue needs bf16 C [n, 2N], no "
                 "accumulation or residual");
-  if (ep.accum) ep.c_f32 = 1;
+  if (ep.accum || sizeof(T) == 4) ep.c_f32 = 1;
   {
     const uintptr_t al = ep.c_f32 ? 15 : 7;
     ep.vec = g.ldc % 4 == 0 && ((uintptr_t)g.C & al) == 0 && ((uintptr_t)g.R & al) == 0 &&
@@ -509,20 +564,25 @@ int gemm(const Gemm &g, hipStream_t s) {
     timing_end(s, tk);
     return check_launch("gemm");
   }
-  // the plain kernel splits float32 outputs stored without gaps
+  // 64 x 64 tiles, in pieces while the chip has CUs to spare and a piece two
+  // k-steps
+  const int tiles = ((g.M + kFTile - 1) / kFTile) * ((g.N + kFTile - 1) / kFTile);
   int S = 1;
-  if (ep.c_f32 && !ep.R && g.ldc == g.N && g.K2 == 0) {
-    S = gemm_split_k(g.M, g.N, g.K);
-    if ((size_t)S * g.M * g.N > cap) S = 1;
-  }
-  const int kps = g.K <= 0 ? 0 : ((g.K + S - 1) / S + 63) / 64 * 64;   // empty: C = R
-  dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, S);
-  gemm_simple_kernel<T><<<grid, 256, 0, s>>>(g.M, g.N, g.K, kps, (const T *)g.A, g.lda,
-                                             g.a_kmajor, (const T *)g.B, g.ldb, g.b_kmajor, ep,
-                                             S > 1 ? g.partial : nullptr, (const T *)g.A2,
-                                             g.lda2, (const T *)g.B2, g.ldb2, g.K2);
-  // fixed-order sum of the split partials into C
-  if (S > 1) splitk_reduce(g.partial, S, (int64_t)g.M * g.N, (float *)g.C, ep.accum != 0, s);
+  if (g.K2 == 0)
+    while (S < gemm_split_k(g.M, g.N, g.K) && tiles * S < 512 &&
+           (size_t)tiles * (S + 1) * (kFTile * kFTile) <= cap)
+      ++S;
+  const int k_piece = ((g.K > 0 ? g.K : 0) + S - 1) / S;
+  const Pieces pc{S > 1 ? 0 : tiles, S > 1 ? tiles : 0, S, (k_piece + kFBK - 1) / kFBK * kFBK,
+                  g.partial};
+  auto operand = [](const void *p, int64_t ld, bool kmajor) {
+    return FOperand{p, ld, kmajor, ld % 4 == 0 && ((uintptr_t)p & (4 * sizeof(T) - 1)) == 0};
+  };
+  gemm_f32_kernel<T><<<pc.whole + pc.rest * S, 256, 0, s>>>(
+      g.M, g.N, g.K > 0 ? g.K : 0, operand(g.A, g.lda, g.a_kmajor),
+      operand(g.B, g.ldb, g.b_kmajor), g.K2, operand(g.A2, g.lda2, g.a_kmajor),
+      operand(g.B2, g.ldb2, g.b_kmajor), ep, pc);
+  if (S > 1) gemm_pieces_kernel<kFTile, kFTile><<<pc.rest * 4, 256, 0, s>>>(ep, pc);
   return check_launch("gemm");
 }
 

@@ -41,7 +41,6 @@ void scale_cast(const float *in, int64_t n, float scale, T *out, T *lo, hipStrea
 void fill_f32(float *p, int64_t n, float v, hipStream_t s);
 // dst[c][r] = src[r][c] for a row-major [rows, cols] matrix of 16-bit elements.
 void transpose16(const void *src, int rows, int cols, void *dst, hipStream_t s);
-void splitk_reduce(const float *part, int S, int64_t n, float *out, bool accumulate, hipStream_t s);
 
 // ---------------------------------------------------------------- GEMM
 // C[M,N] (op) sum_k A(m,k) B(n,k)
@@ -92,13 +91,13 @@ inline size_t gemm_partial_floats(int64_t M, int64_t N) {
   const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
   return (size_t)(tiles * kMaxSplit < 512 ? tiles * kMaxSplit : 512) * 65536;
 }
-// Split factor of the plain kernel for an M x N output over K (K/S >= 4096).
+// The most pieces of a reduction over K whose sums of a whole M x N output fit
+// that scratch, no piece shorter than 64.
 inline int gemm_split_k(int M, int N, int K) {
   const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  if (K < 8192 || tiles > 256) return 1;
-  const int kmax = K / 4096 < kMaxSplit ? K / 4096 : kMaxSplit;
-  const int S = 512 / tiles;
-  return S > kmax ? kmax : S;
+  int S = kMaxSplit < 512 / tiles ? kMaxSplit : 512 / tiles;
+  if (S > K / 64) S = K / 64;
+  return S < 1 ? 1 : S;
 }
 
 // ---------------------------------------------------------------- attention

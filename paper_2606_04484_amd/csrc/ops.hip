@@ -300,15 +300,6 @@ __global__ void fill_kernel(float *p, int64_t n, float v) {
   if (i < n) p[i] = v;
 }
 
-// out[i] += sum_s part[s][i], s ascending.
-__global__ void splitk_reduce_kernel(const float *part, int S, int64_t n, float *out, int accumulate) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float v = accumulate ? out[i] : 0.f;
-  for (int s = 0; s < S; ++s) v += part[(int64_t)s * n + i];
-  out[i] = v;
-}
-
 inline unsigned blocks_for(int64_t n, int per) { return (unsigned)((n + per - 1) / per); }
 
 // ---------------------------------------------------------------- transpose
@@ -434,10 +425,6 @@ void transpose16(const void *src, int rows, int cols, void *dst, hipStream_t s) 
 
 void fill_f32(float *p, int64_t n, float v, hipStream_t s) {
   if (n > 0) fill_kernel<<<blocks_for(n, 256), 256, 0, s>>>(p, n, v);
-}
-
-void splitk_reduce(const float *part, int S, int64_t n, float *out, bool accumulate, hipStream_t s) {
-  if (n > 0) splitk_reduce_kernel<<<blocks_for(n, 256), 256, 0, s>>>(part, S, n, out, accumulate ? 1 : 0);
 }
 
 #define AJ_INST(T)                                                                              \
