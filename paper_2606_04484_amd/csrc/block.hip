@@ -14,8 +14,14 @@ namespace {
 struct Saved {
   void *a, *qkv, *o, *x1, *b, *gu, *s;
   float *rstd1, *lse, *rstd2;
+  float *part;            // scratch of the forward's products (split reductions)
+  size_t part_floats;
   size_t bytes;
 };
+
+// That scratch: enough for 256 pieces of 256 x 256 from 8389 tokens on, and 8 KB
+// per token (a few percent of the arena) below, where tiles are fewer as well.
+size_t fwd_part_floats(int64_t n) { return std::min<int64_t>(2000 * n, 256 * 65536); }
 
 Saved carve_saved(const aj_block_cfg &c, int n, void *base) {
   const size_t es = c.dtype == AJ_BF16 ? 2 : 4;
@@ -33,6 +39,8 @@ Saved carve_saved(const aj_block_cfg &c, int n, void *base) {
   s.rstd1 = cv.take<float>(n);
   s.lse = cv.take<float>((int64_t)c.n_q_heads * n);
   s.rstd2 = cv.take<float>(n);
+  s.part_floats = fwd_part_floats(n);
+  s.part = cv.take<float>(s.part_floats);
   s.bytes = cv.bytes();
   return s;
 }
@@ -221,6 +229,8 @@ int block_fwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
     g.B = tw ? w_t : w_kmajor;
     g.ldb = tw ? g.N : g.K;
     g.b_kmajor = !tw;
+    g.partial = sv.part;
+    g.partial_cap = sv.part_floats;
   };
   rmsnorm_fwd<T>(x, (const T *)w.attn_norm, n, d, c.rms_eps, nullptr, 0, (T *)sv.a, sv.rstd1, st);
   Gemm g;
@@ -282,7 +292,9 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   }
   if (lb && (r = lora_grads<T>(c, *lb, kDown, dy_t, (const T *)sv.s, n, st))) return r;
   g = Gemm();
-  g.M = n; g.N = F; g.K = d; g.A = dy_t; g.lda = d;
+  // every product of the pass may run in pieces
+  auto scratch = [&](Gemm &p) { p.partial = ws.splitk; p.partial_cap = ws.splitk_floats; };
+  g.M = n; g.N = F; g.K = d; g.A = dy_t; g.lda = d; scratch(g);
   g.B = w.w_down; g.ldb = F; g.b_kmajor = false;
   lora_bwd_seg(g, lb, kDown, F);
   if constexpr (sizeof(T) == 2) {
@@ -305,7 +317,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   }
   if (lb && (r = lora_grads<T>(c, *lb, kGu, (const T *)ws.dgu, (const T *)sv.b, n, st))) return r;
   g = Gemm();
-  g.M = n; g.N = d; g.K = 2 * F; g.A = ws.dgu; g.lda = 2 * F;
+  g.M = n; g.N = d; g.K = 2 * F; g.A = ws.dgu; g.lda = 2 * F; scratch(g);
   g.B = w.w_gate_up; g.ldb = d; g.b_kmajor = false; g.C = ws.db; g.ldc = d; g.c_f32 = true;
   lora_bwd_seg(g, lb, kGu, d);
   if ((r = gemm<T>(g, st))) return r;
@@ -324,7 +336,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   }
   if (lb && (r = lora_grads<T>(c, *lb, kO, dx1_t, (const T *)sv.o, n, st))) return r;
   g = Gemm();
-  g.M = n; g.N = hq; g.K = d; g.A = dx1_t; g.lda = d;
+  g.M = n; g.N = hq; g.K = d; g.A = dx1_t; g.lda = d; scratch(g);
   g.B = w.w_o; g.ldb = hq; g.b_kmajor = false; g.C = ws.dout; g.ldc = hq;
   lora_bwd_seg(g, lb, kO, hq);
   if ((r = gemm<T>(g, st))) return r;
@@ -344,7 +356,7 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   if (lb && (r = lora_grads<T>(c, *lb, kQkv, (const T *)ws.dqkv, (const T *)sv.a, n, st)))
     return r;
   g = Gemm();
-  g.M = n; g.N = d; g.K = qdim; g.A = ws.dqkv; g.lda = qdim;
+  g.M = n; g.N = d; g.K = qdim; g.A = ws.dqkv; g.lda = qdim; scratch(g);
   g.B = w.w_qkv; g.ldb = d; g.b_kmajor = false; g.C = ws.da; g.ldc = d; g.c_f32 = true;
   lora_bwd_seg(g, lb, kQkv, d);
   if ((r = gemm<T>(g, st))) return r;
