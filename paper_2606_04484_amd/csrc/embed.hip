@@ -1,12 +1,11 @@
 // Embedding gather x = E[tok] and its backward, the scatter-add
 // dE[v] += sum over positions p with tok[p] == v of dx[p], made
 // deterministic without float atomics:
-//   1. keys (token << 32 | position) are sorted ascending by a bitonic
-//      network (LDS-resident 4096-key chunks, global passes for the longer
-//      strides).  The keys are unique, so the sorted order -- runs of equal
-//      token, positions ascending inside a run -- does not depend on how the
-//      sort is scheduled;
-//   2. the sorted rows are cut into tiles of 256; one wave per (tile,
+//   1. keys (token << 32 | position) are sorted by token with a stable radix
+//      sort, so that the sorted order -- runs of equal token, positions
+//      ascending inside a run -- does not depend on how it is scheduled;
+//   2. the sorted rows are cut into tiles of 256 (64 rows below 65536, so that
+//      small batches fill the chip); one wave per (tile,
 //      256-column slice) walks its rows in order and sums each run of equal
 //      token.  A run that begins and ends inside the tile is added to dE
 //      right there (it has no other owner); the piece of a run that crosses
@@ -23,17 +22,23 @@
 namespace aj {
 namespace {
 
-constexpr int kChunk = 4096;           // keys per LDS-resident bitonic chunk (32 KB)
-constexpr int kSortThreads = 512;
-constexpr int kTile = 256;             // sorted rows per reduction tile
 constexpr int kWaveCols = 256;         // columns per wave: 64 lanes x 4
 constexpr int kTileWaves = 4;
 constexpr uint32_t kNoTok = 0xffffffffu;
 
+// Sorted rows per reduction tile.  A tile is one wave's chain of 8-row batches:
+// at 3443 rows of 128 columns, 14 tiles of 256 rows took 60 us.
+constexpr int kSmallRows = 65536;
+int tile_rows(int n) { return n < kSmallRows ? 64 : 256; }
+int64_t n_tiles(int n) { return (n + tile_rows(n) - 1) / tile_rows(n); }
+
 AJ_DEV uint32_t key_tok(uint64_t k) { return (uint32_t)(k >> 32); }
 AJ_DEV uint32_t key_pos(uint64_t k) { return (uint32_t)k; }
 
-template <typename T>
+// One wave per row.  VEC: 16 bytes per lane and load, all of a lane's loads
+// before its first store (2-byte accesses moved 118943 rows of 3584 bfloat16
+// values in 522 us).
+template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t *tok, int n, const T *emb,
                                                         int d, int vocab, T *x, int32_t *err) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -44,69 +49,152 @@ __global__ __launch_bounds__(256) void embed_fwd_kernel(const int32_t *tok, int 
   if (!ok && lane == 0 && err) atomicOr(err, AJ_DEVERR_TOKEN_RANGE);
   const T *src = emb + (int64_t)(ok ? t : 0) * d;
   T *dst = x + (int64_t)row * d;
-  for (int c = lane; c < d; c += 64) dst[c] = ok ? src[c] : T(0);
-}
-
-// keys[i] = tok << 32 | i for i < n (token field kNoTok when out of range:
-// those rows sort to the end and are skipped); padding up to n2 = all ones.
-__global__ __launch_bounds__(256) void embed_keys_kernel(const int32_t *tok, int n, int n2,
-                                                         int vocab, uint64_t *keys) {
-  for (int i = blockIdx.x * 256 + threadIdx.x; i < n2; i += gridDim.x * 256) {
-    uint64_t k = ~0ull;
-    if (i < n) {
-      const int t = tok[i];
-      const uint32_t tt = (t >= 0 && t < vocab) ? (uint32_t)t : kNoTok;
-      k = ((uint64_t)tt << 32) | (uint32_t)i;
+  if constexpr (VEC) {
+    constexpr int E = 16 / sizeof(T), U = 8;
+    const int nv = d / E;
+    const uint4 *s4 = reinterpret_cast<const uint4 *>(src);
+    uint4 *d4 = reinterpret_cast<uint4 *>(dst);
+    for (int c0 = lane; c0 < nv; c0 += 64 * U) {
+      uint4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        v[u] = ok && c0 + 64 * u < nv ? s4[c0 + 64 * u] : make_uint4(0, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + 64 * u < nv) d4[c0 + 64 * u] = v[u];
     }
-    keys[i] = k;
-  }
-}
-
-// One compare-exchange step (stage k, stride j) over the chunk in LDS; pair
-// q joins i = (q / j) * 2j + q % j with i + j, ascending where bit k of the
-// global index of i is clear.
-AJ_DEV void bitonic_step(uint64_t *s, int64_t base, int k, int j) {
-  const int lj = __ffs(j) - 1;
-  for (int q = threadIdx.x; q < kChunk / 2; q += kSortThreads) {
-    const int i = ((q >> lj) << (lj + 1)) | (q & (j - 1));
-    const bool asc = ((base + i) & k) == 0;
-    const uint64_t a = s[i], b = s[i + j];
-    if ((a > b) == asc) {
-      s[i] = b;
-      s[i + j] = a;
-    }
-  }
-  __syncthreads();
-}
-
-// k_fixed == 0: every stage k <= kChunk of the network on each chunk;
-// else the strides j < kChunk of stage k_fixed (> kChunk).
-__global__ __launch_bounds__(kSortThreads) void bitonic_chunk_kernel(uint64_t *keys, int k_fixed) {
-  __shared__ uint64_t s[kChunk];
-  const int64_t base = (int64_t)blockIdx.x * kChunk;
-  for (int t = threadIdx.x; t < kChunk; t += kSortThreads) s[t] = keys[base + t];
-  __syncthreads();
-  if (k_fixed == 0) {
-    for (int k = 2; k <= kChunk; k <<= 1)
-      for (int j = k >> 1; j > 0; j >>= 1) bitonic_step(s, base, k, j);
   } else {
-    for (int j = kChunk >> 1; j > 0; j >>= 1) bitonic_step(s, base, k_fixed, j);
+    for (int c = lane; c < d; c += 64) dst[c] = ok ? src[c] : T(0);
   }
-  for (int t = threadIdx.x; t < kChunk; t += kSortThreads) keys[base + t] = s[t];
 }
 
-// One global compare-exchange step (stride j >= kChunk) of stage k.
-__global__ __launch_bounds__(256) void bitonic_global_kernel(uint64_t *keys, int half, int k,
-                                                             int j) {
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= half) return;
-  const int lj = __ffs(j) - 1;
-  const int i = ((q >> lj) << (lj + 1)) | (q & (j - 1));
-  const bool asc = (i & k) == 0;
-  const uint64_t a = keys[i], b = keys[i + j];
-  if ((a > b) == asc) {
-    keys[i] = b;
-    keys[i + j] = a;
+// ---------------------------------------------------------------- sort
+// Least significant digit first, one count and one scatter launch per digit of
+// up to 9 bits (two digits for a 152064-word vocab).  At most 64 workgroups (256
+// past 262144 rows) take a contiguous share of the rows each, so that a scatter
+// workgroup can add up the counts before its own by itself: no scan launch, no
+// workgroup waits for another.  118943 rows: 22 launches of a bitonic network
+// 166 us, these 4 launches 33 us.
+constexpr int kMaxBits = 9, kMaxBins = 1 << kMaxBits;
+constexpr int kSub = 1024;             // rows per round of a workgroup: 256 per wave
+
+int sort_blocks(int n) {
+  const int most = n > 262144 ? 256 : 64;
+  const int64_t b = ((int64_t)n + kSub - 1) / kSub;
+  return (int)(b < most ? b : most);
+}
+
+struct Digit { int shift, bits, vocab; };
+
+// Row i's key of the first pass (tok) or a later one; tokens out of range take
+// the token field kNoTok and sort to the end, as value `vocab`.
+AJ_DEV uint64_t sort_key(const int32_t *tok, const uint64_t *keys, int64_t i, int vocab) {
+  if (!tok) return keys[i];
+  const int t = tok[i];
+  const uint32_t tt = t >= 0 && t < vocab ? (uint32_t)t : kNoTok;
+  return ((uint64_t)tt << 32) | (uint32_t)i;
+}
+AJ_DEV int digit_of(uint64_t key, const Digit &dg) {
+  const uint32_t t = key_tok(key), v = t == kNoTok ? (uint32_t)dg.vocab : t;
+  return (int)((v >> dg.shift) & ((1u << dg.bits) - 1));
+}
+
+// counts[block][bin] of the block's rows
+__global__ __launch_bounds__(256) void sort_count_kernel(const int32_t *tok, const uint64_t *keys,
+                                                         int n, Digit dg, int share,
+                                                         int32_t *counts) {
+  __shared__ int32_t cnt[kMaxBins];
+  const int bins = 1 << dg.bits;
+  for (int b = threadIdx.x; b < bins; b += 256) cnt[b] = 0;
+  __syncthreads();
+  const int64_t lo = (int64_t)blockIdx.x * share, hi = min(lo + share, (int64_t)n);
+  for (int64_t i = lo + threadIdx.x; i < hi; i += 256)
+    atomicAdd(&cnt[digit_of(sort_key(tok, keys, i, dg.vocab), dg)], 1);
+  __syncthreads();
+  for (int b = threadIdx.x; b < bins; b += 256) counts[blockIdx.x * bins + b] = cnt[b];
+}
+
+// Stable scatter of the block's rows.  A round takes 1024 of them, 256 per wave
+// in row order: a lane's rank among the wave's equal digits comes from ballots
+// and the wave's running counts, and the rank of the wave's share from the
+// counts of the waves before it.
+__global__ __launch_bounds__(256) void sort_scatter_kernel(const int32_t *tok, const uint64_t *keys,
+                                                           int n, Digit dg, int share,
+                                                           const int32_t *counts, uint64_t *out) {
+  __shared__ int32_t base[kMaxBins];          // next output row of each digit
+  __shared__ int32_t wcnt[4][kMaxBins];
+  __shared__ int32_t part[4];
+  const int bins = 1 << dg.bits, nb = gridDim.x, me = blockIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // this thread's digits: 2 tid and 2 tid + 1
+  int before[2] = {0, 0}, all[2] = {0, 0};
+  for (int b0 = 0; b0 < nb; b0 += 8) {
+    int c[8][2];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int bin = 2 * (int)threadIdx.x + e;
+        c[u][e] = b0 + u < nb && bin < bins ? counts[(b0 + u) * bins + bin] : 0;
+      }
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        all[e] += c[u][e];
+        before[e] += b0 + u < me ? c[u][e] : 0;
+      }
+  }
+  int x = all[0] + all[1];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) part[w] = x;
+  __syncthreads();
+  int off = x - all[0] - all[1];
+  for (int i = 0; i < w; ++i) off += part[i];
+  if (2 * (int)threadIdx.x < bins) base[2 * threadIdx.x] = off + before[0];
+  if (2 * (int)threadIdx.x + 1 < bins) base[2 * threadIdx.x + 1] = off + all[0] + before[1];
+  const int64_t lo = (int64_t)me * share, hi = min(lo + share, (int64_t)n);
+  for (int64_t r0 = lo; r0 < hi; r0 += kSub) {
+    for (int b = threadIdx.x; b < 4 * kMaxBins; b += 256) (&wcnt[0][0])[b] = 0;
+    __syncthreads();
+    uint64_t key[4];
+    int dig[4], rank[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t i = r0 + w * 256 + q * 64 + lane;
+      key[q] = i < hi ? sort_key(tok, keys, i, dg.vocab) : 0;
+      dig[q] = i < hi ? digit_of(key[q], dg) : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint64_t peers = __ballot(dig[q] >= 0);
+      for (int b = 0; b < dg.bits; ++b) {
+        const uint64_t set = __ballot((dig[q] >> b) & 1);
+        peers &= (dig[q] >> b) & 1 ? set : ~set;
+      }
+      const int below = __popcll(peers & ((1ull << lane) - 1));
+      rank[q] = dig[q] >= 0 ? wcnt[w][dig[q]] + below : 0;
+      // every lane has read its count (one wave, in order) before a leader adds
+      __builtin_amdgcn_wave_barrier();
+      if (dig[q] >= 0 && below == 0) wcnt[w][dig[q]] += __popcll(peers);
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (dig[q] < 0) continue;
+      int at = base[dig[q]] + rank[q];
+      for (int i = 0; i < w; ++i) at += wcnt[i][dig[q]];
+      out[at] = key[q];
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < bins; b += 256)
+      base[b] += wcnt[0][b] + wcnt[1][b] + wcnt[2][b] + wcnt[3][b];
+    __syncthreads();
   }
 }
 
@@ -116,6 +204,7 @@ AJ_DEV void add4(float4 &a, const float4 &b) {
 
 // Step 2: one wave per (tile, 256-column slice); lane l owns columns
 // col0 .. col0+3.  piece: [n_tiles][2][d].
+template <int kTile>
 __global__ __launch_bounds__(256) void embed_tile_kernel(const uint64_t *keys, int n,
                                                          const float *dx, int d, float *demb,
                                                          float *piece) {
@@ -176,6 +265,7 @@ __global__ __launch_bounds__(256) void embed_tile_kernel(const uint64_t *keys, i
 
 // Step 3: the run crossing boundary b = (blockIdx.x + 1) * kTile, if it
 // crosses no earlier boundary; one thread per 4 columns.
+template <int kTile>
 __global__ __launch_bounds__(256) void embed_cross_kernel(const uint64_t *keys, int n, int n_tiles,
                                                           int d, const float *piece, float *demb) {
   const int bt = blockIdx.x + 1;
@@ -198,14 +288,9 @@ __global__ __launch_bounds__(256) void embed_cross_kernel(const uint64_t *keys, 
   *o = v;
 }
 
-int64_t sort_len(int n) {
-  int64_t n2 = kChunk;
-  while (n2 < n) n2 <<= 1;
-  return n2;
-}
-
 struct EmbedWs {
-  uint64_t *keys;
+  uint64_t *keys[2];
+  int32_t *counts;
   float *piece;
   size_t bytes;
 };
@@ -213,11 +298,25 @@ struct EmbedWs {
 EmbedWs carve_embed(void *ws, int n, int d) {
   Carver c(ws);
   EmbedWs w;
-  w.keys = c.take<uint64_t>(sort_len(n));
-  const int64_t tiles = (n + kTile - 1) / kTile;
+  w.keys[0] = c.take<uint64_t>(n);
+  w.keys[1] = c.take<uint64_t>(n);
+  w.counts = c.take<int32_t>((int64_t)sort_blocks(n) * kMaxBins);
+  // never less for more rows: a buffer sized for the largest pack serves them all
+  const int64_t tiles = n < kSmallRows ? n_tiles(n) : std::max<int64_t>(n_tiles(n), kSmallRows / 64);
   w.piece = c.take<float>(2 * tiles * (int64_t)d);
   w.bytes = c.bytes();
   return w;
+}
+
+template <int kTile>
+void embed_reduce(const uint64_t *keys, int n, const float *dx, int d, float *d_emb, float *piece,
+                  hipStream_t s) {
+  const int tiles = (n + kTile - 1) / kTile;
+  const int col_blocks = (d + kTileWaves * kWaveCols - 1) / (kTileWaves * kWaveCols);
+  embed_tile_kernel<kTile><<<dim3(tiles, col_blocks), 256, 0, s>>>(keys, n, dx, d, d_emb, piece);
+  if (tiles > 1)
+    embed_cross_kernel<kTile><<<dim3(tiles - 1, (d / 4 + 255) / 256), 256, 0, s>>>(
+        keys, n, tiles, d, piece, d_emb);
 }
 
 }  // namespace
@@ -225,7 +324,10 @@ EmbedWs carve_embed(void *ws, int n, int d) {
 template <typename T>
 void embed_fwd(const int32_t *tok, int n, const T *emb, int d, int vocab, T *x, int32_t *err,
                hipStream_t s) {
-  if (n > 0) embed_fwd_kernel<T><<<(n + 3) / 4, 256, 0, s>>>(tok, n, emb, d, vocab, x, err);
+  if (n <= 0) return;
+  const bool vec = (d * sizeof(T)) % 16 == 0 && (((uintptr_t)emb | (uintptr_t)x) & 15) == 0;
+  if (vec) embed_fwd_kernel<T, true><<<(n + 3) / 4, 256, 0, s>>>(tok, n, emb, d, vocab, x, err);
+  else embed_fwd_kernel<T, false><<<(n + 3) / 4, 256, 0, s>>>(tok, n, emb, d, vocab, x, err);
 }
 template void embed_fwd<float>(const int32_t *, int, const float *, int, int, float *, int32_t *,
                                hipStream_t);
@@ -269,22 +371,21 @@ extern "C" int aj_embed_bwd(const int32_t *tok, int32_t n_tok, const float *dx, 
   AJ_REQUIRE(ws_bytes >= w.bytes, AJ_ERR_WORKSPACE, "aj_embed_bwd: workspace %zu < %zu",
              ws_bytes, w.bytes);
   hipStream_t s = (hipStream_t)stream;
-  const int64_t n2 = sort_len(n_tok);
-  embed_keys_kernel<<<(int)std::min<int64_t>((n2 + 255) / 256, 4096), 256, 0, s>>>(
-      tok, n_tok, (int)n2, vocab, w.keys);
-  const int chunks = (int)(n2 / kChunk);
-  bitonic_chunk_kernel<<<chunks, kSortThreads, 0, s>>>(w.keys, 0);
-  for (int64_t k = 2 * kChunk; k <= n2; k <<= 1) {
-    for (int64_t j = k >> 1; j >= kChunk; j >>= 1)
-      bitonic_global_kernel<<<(int)((n2 / 2 + 255) / 256), 256, 0, s>>>(w.keys, (int)(n2 / 2),
-                                                                          (int)k, (int)j);
-    bitonic_chunk_kernel<<<chunks, kSortThreads, 0, s>>>(w.keys, (int)k);
+  // as few digits of the token (and of the value `vocab` past the last one) as
+  // kMaxBits allows, evenly wide
+  int bits = 1;
+  while (bits < 31 && (vocab >> bits) != 0) ++bits;
+  const int passes = (bits + kMaxBits - 1) / kMaxBits, width = (bits + passes - 1) / passes;
+  const int blocks = sort_blocks(n_tok), share = (n_tok + blocks - 1) / blocks;
+  for (int p = 0; p < passes; ++p) {
+    const Digit dg{p * width, width, vocab};
+    const int32_t *t = p == 0 ? tok : nullptr;
+    sort_count_kernel<<<blocks, 256, 0, s>>>(t, w.keys[(p & 1) ^ 1], n_tok, dg, share, w.counts);
+    sort_scatter_kernel<<<blocks, 256, 0, s>>>(t, w.keys[(p & 1) ^ 1], n_tok, dg, share, w.counts,
+                                               w.keys[p & 1]);
   }
-  const int tiles = (n_tok + kTile - 1) / kTile;
-  const int col_blocks = (d + kTileWaves * kWaveCols - 1) / (kTileWaves * kWaveCols);
-  embed_tile_kernel<<<dim3(tiles, col_blocks), 256, 0, s>>>(w.keys, n_tok, dx, d, d_emb, w.piece);
-  if (tiles > 1)
-    embed_cross_kernel<<<dim3(tiles - 1, (d / 4 + 255) / 256), 256, 0, s>>>(
-        w.keys, n_tok, tiles, d, w.piece, d_emb);
+  const uint64_t *keys = w.keys[(passes - 1) & 1];
+  if (tile_rows(n_tok) == 64) embed_reduce<64>(keys, n_tok, dx, d, d_emb, w.piece, s);
+  else embed_reduce<256>(keys, n_tok, dx, d, d_emb, w.piece, s);
   return check_launch("aj_embed_bwd");
 }

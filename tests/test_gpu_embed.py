@@ -98,3 +98,44 @@ def test_embed_fwd_gathers_rows():
     np.testing.assert_array_equal(got[:4], emb[tok[:4]])
     assert not np.any(got[4])
     assert int(err.cpu()[0]) == 1        # AJ_DEVERR_TOKEN_RANGE: token 300 is out of range
+
+
+@pytest.mark.parametrize("n,vocab", [(1023, 1), (1025, 2), (64 * 1024, 511), (65535, 512), (65536, 513),
+                                     (65 * 1024 + 1, 262143), (3000, 262144), (262145, 3000000)])
+def test_embed_bwd_sort_edges(n, vocab):
+    """One to three digits of the sort, the value `vocab` (tokens out of range) with
+    and without a digit of its own, shares of one round and more, 64 and 256
+    workgroups, both tile sizes: the scatter-add and bit-identical repeats."""
+    from paper_2606_04484_amd import capi
+    rng = np.random.default_rng(n)
+    print(f"embed sort n={n} vocab={vocab}", flush=True)
+    tok = rng.integers(0, vocab, n).astype(np.int32)
+    tok[rng.integers(0, n, n // 50)] = rng.choice([-1, vocab, vocab + 5], n // 50)
+    tok[n // 2:n // 2 + n // 4] = tok[0] if 0 <= tok[0] < vocab else 0        # a long run
+    dx = rng.standard_normal((n, 8)).astype(np.float32)
+    tok_d, dx_d = torch.from_numpy(tok).cuda(), torch.from_numpy(dx).cuda()
+    outs = []
+    for _ in range(2):
+        g = torch.zeros(vocab, 8, device="cuda")
+        _bwd(capi, tok_d, dx_d, g)
+        outs.append(g.cpu().numpy())
+    assert np.array_equal(outs[0], outs[1])
+    ok = (tok >= 0) & (tok < vocab)
+    ref, scale = np.zeros((vocab, 8)), np.zeros((vocab, 8))
+    np.add.at(ref, tok[ok], dx[ok].astype(np.float64))
+    np.add.at(scale, tok[ok], np.abs(dx[ok]).astype(np.float64))
+    assert np.max(np.abs(outs[0] - ref) / (scale + 1e-30)) <= 1e-5
+
+
+@pytest.mark.parametrize("d", [4, 24, 25, 520, 4104, 8200])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_embed_fwd_widths(d, dtype):
+    """Rows of whole 16-byte pieces and not, up to more than one batch of loads."""
+    from paper_2606_04484_amd import capi
+    g = torch.Generator(device="cuda").manual_seed(d)
+    emb = torch.randn(50, d, device="cuda", generator=g).to(dtype)
+    tok = torch.tensor([3, 49, 0, 50, 3, -1, 7], dtype=torch.int32, device="cuda")
+    x = torch.full((7, d), 9.0, device="cuda", dtype=dtype)
+    capi.aj_embed_fwd(tok, emb, x, None)
+    ok = ((tok >= 0) & (tok < 50)).unsqueeze(1)
+    assert torch.equal(x, torch.where(ok, emb[tok.clamp(0, 49).long()], torch.zeros((), dtype=dtype, device="cuda")))
