@@ -220,47 +220,47 @@ __global__ __launch_bounds__(256) void embed_tile_kernel(const uint64_t *keys, i
   const uint32_t next_tok = r1 < n ? key_tok(keys[r1]) : kNoTok;
   float *slot0 = piece + ((int64_t)tile * 2) * d + col0;
   float *slot1 = slot0 + d;
-  uint32_t cur = key_tok(sk[0]);
-  bool began_before = cur == prev_tok;         // the first run started in an earlier tile
+  // the first run may have started in an earlier tile
+  bool began_before = key_tok(sk[0]) == prev_tok;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  auto flush = [&](bool continues) {
-    if (cur == kNoTok) return;
-    if (began_before) {
-      *(float4 *)slot0 = acc;                    // head piece (or the whole tile)
-    } else if (continues) {
-      *(float4 *)slot1 = acc;                    // tail piece of a run that begins here
-    } else {
-      float4 *o = (float4 *)(demb + (int64_t)cur * d + col0);
-      float4 v = *o;
-      add4(v, acc);
-      *o = v;
-    }
-  };
   for (int r = r0; r < r1; r += 8) {
-    float4 v[8];
+    // eight rows, and the dE rows of the runs that end among them, in flight at once
+    float4 v[8], o[8];
     uint32_t tt[8];
+    bool last[8];       // the row is the last of its run
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const int rr = r + u;
       const uint64_t k = rr < r1 ? sk[rr - r0] : ~0ull;
       tt[u] = key_tok(k);
-      v[u] = (rr < r1 && tt[u] != kNoTok)
-                 ? *(const float4 *)(dx + (int64_t)key_pos(k) * d + col0)
-                 : make_float4(0.f, 0.f, 0.f, 0.f);
+      last[u] = tt[u] != (rr + 1 < r1 ? key_tok(sk[rr + 1 - r0]) : next_tok);
+      const bool in = rr < r1 && tt[u] != kNoTok;
+      v[u] = in ? *(const float4 *)(dx + (int64_t)key_pos(k) * d + col0)
+                : make_float4(0.f, 0.f, 0.f, 0.f);
+      o[u] = in && last[u] ? *(const float4 *)(demb + (int64_t)tt[u] * d + col0)
+                           : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      if (r + u >= r1) break;
-      if (tt[u] != cur) {
-        flush(false);
-        cur = tt[u];
+      if (r + u >= r1 || tt[u] == kNoTok) break;
+      add4(acc, v[u]);
+      if (last[u]) {
+        if (began_before) {
+          *(float4 *)slot0 = acc;                // head piece
+        } else {
+          add4(o[u], acc);
+          *(float4 *)(demb + (int64_t)tt[u] * d + col0) = o[u];
+        }
+      } else if (r + u + 1 == r1) {
+        // the run goes on in the next tile: the whole tile, or a tail piece
+        *(float4 *)(began_before ? slot0 : slot1) = acc;
+      }
+      if (last[u]) {
         began_before = false;
         acc = make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      add4(acc, v[u]);
     }
   }
-  flush(cur == next_tok);
 }
 
 // Step 3: the run crossing boundary b = (blockIdx.x + 1) * kTile, if it
