@@ -193,3 +193,28 @@ def test_adamw_full_parameter_count():
                 rp, rm, rv, m0, g0)
     np.testing.assert_array_equal(cp[idx].float().cpu().numpy(),
                                   bf16_round(P[idx].cpu().numpy()))
+
+
+@pytest.mark.parametrize("extra,copy", [(0, None), (1, torch.float32), (3, torch.bfloat16)])
+def test_adamw_either_side_of_the_cached_size(extra, copy):
+    """The streaming path (more than 2^24 parameters) and the cached one give the
+    same values bit for bit, remainders of four included."""
+    from paper_2606_04484_amd import capi
+    n = (1 << 24) + 4 + extra
+    gen = torch.Generator(device="cuda").manual_seed(extra)
+    src = [torch.randn(n, generator=gen, device="cuda") * s for s in (0.02, 1e-3, 1e-4)]
+    src.append(torch.rand(n, generator=gen, device="cuda") * 1e-6)
+    hp = (2e-4, 0.9, 0.95, 1e-8, 0.1, 3)
+    outs = []
+    for parts in (1, 2):
+        p, g, m, v = (t.clone() for t in src)
+        c = None if copy is None else torch.zeros(n, dtype=copy, device="cuda")
+        half = n if parts == 1 else n // 8 * 4
+        for a, b in ((0, half), (half, n)):
+            if b > a:
+                capi.aj_adamw_step(p[a:b], g[a:b], m[a:b], v[a:b], *hp,
+                                   param_copy=None if c is None else c[a:b])
+        outs.append([p, m, v] + ([] if c is None else [c]))
+    torch.cuda.synchronize()
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
