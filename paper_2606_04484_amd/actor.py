@@ -74,6 +74,10 @@ class Merger:
     """Owns the output and workspace buffers of aj_merge_timelines (text=False) or
     aj_merge_timelines_text (text=True: Match on tl_dev["blk_text"]) for one input size."""
 
+    # Up to this many timelines the offsets come back whole with the counts, in one
+    # wait (0.5 MB more at the most); past it the counts first, then what they say.
+    ONE_COPY_TL = 65536
+
     def __init__(self, tl_dev, text=False):
         dev = tl_dev["tok"].device
         n_traj = tl_dev["traj_tl_off"].numel() - 1
@@ -96,6 +100,12 @@ class Merger:
             "targets": torch.empty(cap, **i32),
         }
         self.err = torch.zeros(1, **i32)
+        # pinned landing place of counts, cu_seqlens and cu_targets (see layout)
+        self.host = None
+        if n_tl <= self.ONE_COPY_TL:
+            pin = lambda n, dt: torch.empty(n, dtype=dt, pin_memory=dev.type == "cuda")
+            self.host = (pin(4, torch.int64), pin(n_tl + 1, torch.int32),
+                         pin(n_tl + 1, torch.int32))
         self.text = text
         if text:
             n_blk = tl_dev["blk_text"].numel()
@@ -116,19 +126,28 @@ class Merger:
         fn(self.tl, self.out, self.err, self.ws)
 
     def layout(self, pack_tokens):
-        """Reads the counts back (one synchronisation) and plans the packs."""
-        counts = self.out["counts"].cpu().tolist()
-        n_seg, n_tok, n_mask, max_seqlen = (int(v) for v in counts)
-        cu = self.out["cu_seqlens"][:n_seg + 1].cpu()
-        cut = self.out["cu_targets"][:n_seg + 1].cpu().numpy()
-        L = Layout(self.out, n_seg, n_tok, n_mask, max_seqlen, cu.numpy(), cut)
+        """Reads the counts and segment offsets back (one synchronisation for up to
+        ONE_COPY_TL timelines) and plans the packs."""
+        o = self.out
+        if self.host is not None:
+            src = (o["counts"], o["cu_seqlens"], o["cu_targets"])
+            for h, d in zip(self.host, src):
+                h.copy_(d, non_blocking=True)
+            torch.cuda.current_stream(o["counts"].device).synchronize()
+            n_seg, n_tok, n_mask, max_seqlen = self.host[0].tolist()
+            cu, cut = (h[:n_seg + 1].numpy().copy() for h in self.host[1:])
+        else:
+            n_seg, n_tok, n_mask, max_seqlen = (int(v) for v in o["counts"].cpu().tolist())
+            cu = o["cu_seqlens"][:n_seg + 1].cpu().numpy()
+            cut = o["cu_targets"][:n_seg + 1].cpu().numpy()
+        L = Layout(o, n_seg, n_tok, n_mask, max_seqlen, cu, cut)
         if n_seg:
-            offs = C.aj_plan_packs(cu, pack_tokens)
-            cuh = cu.numpy()
-            for a, b in zip(offs[:-1], offs[1:]):
-                lens = np.diff(cuh[a:b + 1])
-                L.packs.append(dict(s0=a, s1=b, t0=int(cuh[a]), t1=int(cuh[b]), r0=int(cut[a]),
-                                    r1=int(cut[b]), max_len=int(lens.max())))
+            offs = C.aj_plan_packs(torch.from_numpy(cu), pack_tokens)
+            t, r = cu[offs].tolist(), cut[offs].tolist()
+            longest = np.maximum.reduceat(np.diff(cu), offs[:-1]).tolist()
+            L.packs = [dict(s0=a, s1=b, t0=t[i], t1=t[i + 1], r0=r[i], r1=r[i + 1],
+                            max_len=longest[i])
+                       for i, (a, b) in enumerate(zip(offs[:-1], offs[1:]))]
         return L
 
     def device_error(self):
