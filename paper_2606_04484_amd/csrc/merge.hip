@@ -62,7 +62,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kChunk = 1024;          // tokens per workgroup in the block-start compaction
+constexpr int kChunk = 16 * kBlock;   // tokens per workgroup in the block-start compaction
 constexpr int kCmpChunk = 2048;       // tokens per compare item: 32 rows of 64
 constexpr int kRows = kCmpChunk / 64;                  // llm rows of 64 positions per item
 constexpr int kRowsPerLane = (kRows + 63) / 64;        // rows per lane of a wavefront
@@ -1137,41 +1137,56 @@ AJ_DEV int upper_index(const int32_t *off, int64_t v, int lo, int hi) {
   return lo;
 }
 
+// Block-start bits of the thread's 16 tokens from u0 on (bit r: token u0 + r),
+// by aligned dwords except at the input's ragged end.
+AJ_DEV uint32_t block_start_bits(const MergeArgs &a, int64_t u0) {
+  uint32_t bits = 0;
+  if (u0 + 16 <= a.n_tok) {
+    uint32_t f[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = load_flags4(a.flags + u0 + 4 * q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t m = (f[q] >> 2) & 0x01010101u;   // AJ_FLAG_BLOCK_START is bit 2
+      bits |= ((m & 1u) | ((m >> 7) & 2u) | ((m >> 14) & 4u) | ((m >> 21) & 8u)) << (4 * q);
+    }
+  } else {
+    for (int r = 0; r < 16 && u0 + r < a.n_tok; ++r)
+      bits |= (uint32_t)((a.flags[u0 + r] & AJ_FLAG_BLOCK_START) != 0) << r;
+  }
+  return bits;
+}
+
 // Block starts per chunk of kChunk tokens.
 __global__ __launch_bounds__(kBlock) void blk_count_kernel(MergeArgs a) {
-  const int64_t u0 = (int64_t)blockIdx.x * kChunk + threadIdx.x * 4;
-  int c = 0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-    c += (u0 + r < a.n_tok) && (a.flags[u0 + r] & AJ_FLAG_BLOCK_START);
+  const int64_t u0 = (int64_t)blockIdx.x * kChunk + threadIdx.x * 16;
   int tot;
-  block_scan_incl<kBlock>(c, &tot);
+  block_scan_incl<kBlock>(__popc(block_start_bits(a, u0)), &tot);
   if (threadIdx.x == 0) a.chunk_cnt[blockIdx.x] = tot;
 }
 
 // blk_start[b] = first token of block b (the scan checked there are n_blk).
 __global__ __launch_bounds__(kBlock) void blk_write_kernel(MergeArgs a) {
   if (fatal(a)) return;
-  const int64_t u0 = (int64_t)blockIdx.x * kChunk + threadIdx.x * 4;
-  int f[4], c = 0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    f[r] = (u0 + r < a.n_tok) && (a.flags[u0 + r] & AJ_FLAG_BLOCK_START);
-    c += f[r];
-  }
+  const int64_t u0 = (int64_t)blockIdx.x * kChunk + threadIdx.x * 16;
+  uint32_t bits = block_start_bits(a, u0);
+  const int c = __popc(bits);
   int tot;
-  int incl = block_scan_incl<kBlock>(c, &tot);
-  int w = a.chunk_off[blockIdx.x] + incl - c;
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-    if (f[r]) a.blk_start[w++] = (int32_t)(u0 + r);
+  int w = a.chunk_off[blockIdx.x] + block_scan_incl<kBlock>(c, &tot) - c;
+  for (; bits; bits &= bits - 1) a.blk_start[w++] = (int32_t)(u0 + __ffs(bits) - 1);
   if (blockIdx.x == 0 && threadIdx.x == 0) a.blk_start[a.n_blk] = (int32_t)a.n_tok;
 }
 
-// tl_blk[i] = the block that starts at timeline i's first token.
+// tl_blk[i] = the block that starts at timeline i's first token; every block's
+// votes and destination cleared.
 __global__ void tl_blk_kernel(MergeArgs a) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i > a.n_tl || fatal(a)) return;
+  if (fatal(a)) return;
+  if (i < a.n_blk) {
+    a.blk_claim[i] = -1;
+    a.dst_off[i] = -1;
+  }
+  if (i > a.n_tl) return;
   if (i == a.n_tl) { a.tl_blk[i] = a.n_blk; return; }
   const int64_t u = a.tl_tok_off[i];
   int lo = 0, hi = a.n_blk;          // first block starting at or after u
@@ -1183,16 +1198,9 @@ __global__ void tl_blk_kernel(MergeArgs a) {
   a.tl_blk[i] = lo;
 }
 
-__global__ void blk_tl_kernel(MergeArgs a) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= a.n_blk || fatal(a)) return;
-  a.blk_tl[b] = upper_index(a.tl_blk, b, 0, a.n_tl - 1);
-  a.blk_claim[b] = -1;
-  a.dst_off[b] = -1;
-}
-
 // One wavefront per timeline j: candidates from the episode's last timeline
-// down, key comparison with early exit.
+// down, key comparison with early exit.  Then j's blocks get their timeline, and
+// the llm ones of an absorbed j vote for the survivor block they align with.
 __global__ __launch_bounds__(64) void find_absorber_text_kernel(MergeArgs a) {
   const int j = blockIdx.x;
   if (fatal(a)) {
@@ -1220,16 +1228,11 @@ __global__ __launch_bounds__(64) void find_absorber_text_kernel(MergeArgs a) {
     if (equal) { result = i; break; }
   }
   if (threadIdx.x == 0) a.absorber[j] = result;
-}
-
-// llm blocks of absorbed timelines vote for the survivor block they align with.
-__global__ void claim_text_kernel(MergeArgs a) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= a.n_blk || fatal(a)) return;
-  const int t = a.blk_tl[b];
-  const int s = a.absorber[t];
-  if (s < 0 || !llm_block(a, b)) return;
-  atomicMax(&a.blk_claim[a.tl_blk[s] + (b - a.tl_blk[t])], t);
+  const int bs = result >= 0 ? a.tl_blk[result] : 0;
+  for (int k = threadIdx.x; k < nj; k += 64) {
+    a.blk_tl[bj + k] = j;
+    if (result >= 0 && llm_block(a, bj + k)) atomicMax(&a.blk_claim[bs + k], j);
+  }
 }
 
 // Source block and output length of every block (0 for absorbed timelines).
@@ -1247,49 +1250,61 @@ __global__ void select_text_kernel(MergeArgs a) {
   a.blk_off[b] = src >= 0 ? a.blk_start[src + 1] - a.blk_start[src] : 0;
 }
 
-// Single workgroup of 1024 threads: output offsets of the blocks (exclusive
-// scan of their lengths, in place), then the survivor scan as in resolve.
+// Single workgroup of 1024 threads, 8 items per thread a round: output offsets of
+// the blocks (exclusive scan of their lengths, in place), then the survivor scan
+// as in resolve.
 __global__ __launch_bounds__(1024) void resolve_text_kernel(MergeArgs a) {
-  __shared__ int carry_seg, carry_tok, carry_max;
-  if (threadIdx.x == 0) { carry_seg = 0; carry_tok = 0; carry_max = 0; }
-  __syncthreads();
+  constexpr int K = 8;
+  __shared__ int carry_max;
+  if (threadIdx.x == 0) carry_max = 0;
   const bool bad = fatal(a);
-  if (!bad) {
-    for (int base = 0; base < a.n_blk; base += 1024) {
-      const int b = base + threadIdx.x;
-      const int len = b < a.n_blk ? a.blk_off[b] : 0;
-      int tot;
-      const int incl = block_scan_incl<1024>(len, &tot);
-      if (b < a.n_blk) a.blk_off[b] = carry_tok + incl - len;
-      __syncthreads();
-      if (threadIdx.x == 0) carry_tok += tot;
-      __syncthreads();
+  const int i0 = (threadIdx.x >> 6) * 64 * K + (threadIdx.x & 63);   // item r: i0 + 64 r
+  int carry_tok = 0, carry_seg = 0;
+  for (int base = 0; !bad && base < a.n_blk; base += 1024 * K) {
+    int v[K];
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int b = base + i0 + 64 * r;
+      v[r] = b < a.n_blk ? a.blk_off[b] : 0;
     }
-    if (threadIdx.x == 0) a.blk_off[a.n_blk] = carry_tok;
+    carry_tok += wave_items_scan<1024, K>(v, carry_tok);
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int b = base + i0 + 64 * r;
+      if (b < a.n_blk) a.blk_off[b] = v[r];
+    }
   }
+  if (!bad && threadIdx.x == 0) a.blk_off[a.n_blk] = carry_tok;
   // the block offsets written above are read back by other threads
   __syncthreads();
-  for (int base = 0; base < a.n_tl; base += 1024) {
-    const int i = base + threadIdx.x;
-    const int surv = !bad && i < a.n_tl && a.absorber[i] < 0;
-    int tot_s;
-    const int is = block_scan_incl<1024>(surv, &tot_s);
-    if (i < a.n_tl) {
-      if (surv) {
-        const int seg = carry_seg + is - 1;
+  int mx = 0;
+  for (int base = 0; base < a.n_tl; base += 1024 * K) {
+    int v[K];
+    uint32_t surv = 0;
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int i = base + i0 + 64 * r;
+      v[r] = !bad && i < a.n_tl && a.absorber[i] < 0;
+      surv |= (uint32_t)v[r] << r;
+    }
+    carry_seg += wave_items_scan<1024, K>(v, carry_seg);
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+      const int i = base + i0 + 64 * r;
+      if (i >= a.n_tl) continue;
+      if ((surv >> r) & 1) {
         const int o0 = a.blk_off[a.tl_blk[i]];
-        a.tl_seg[i] = seg;
-        a.seg_src[seg] = i;
-        a.cu_seqlens[seg] = o0;
-        atomicMax(&carry_max, a.blk_off[a.tl_blk[i + 1]] - o0);
+        a.tl_seg[i] = v[r];
+        a.seg_src[v[r]] = i;
+        a.cu_seqlens[v[r]] = o0;
+        mx = max(mx, a.blk_off[a.tl_blk[i + 1]] - o0);
       } else {
         a.tl_seg[i] = -1;
       }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) carry_seg += tot_s;
-    __syncthreads();
   }
+  if (mx > 0) atomicMax(&carry_max, mx);
+  __syncthreads();
   if (threadIdx.x == 0) {
     const int n_out = bad ? 0 : carry_tok;
     a.cu_seqlens[carry_seg] = n_out;
@@ -1311,36 +1326,100 @@ __global__ void place_text_kernel(MergeArgs a) {
   a.dst_pos[src] = o - a.blk_off[a.tl_blk[a.blk_tl[b]]];
 }
 
-// One thread per input token: copy it to where its block lands, if anywhere.
+// kEmitSpan input tokens per workgroup, 8 per thread, copied to where their block
+// lands, if anywhere.  One wavefront finds the span's first block (64 probes a
+// step) and puts the next 64 blocks in LDS; spans of more blocks search per
+// token.  (A thread searching for every 256 tokens: 43 us for 6.1M tokens of 6280
+// blocks, of which it copies 1.4M; this one 21 us.)
 __global__ __launch_bounds__(kBlock) void emit_text_kernel(MergeArgs a) {
   if (fatal(a)) return;
-  const int64_t u0 = (int64_t)blockIdx.x * blockDim.x;
-  __shared__ int r[2];
-  if (threadIdx.x == 0) {
-    int64_t u1 = u0 + blockDim.x - 1;
-    if (u1 >= a.n_tok) u1 = a.n_tok - 1;
-    r[0] = upper_index(a.blk_start, u0, 0, a.n_blk - 1);
-    r[1] = upper_index(a.blk_start, u1, r[0], a.n_blk - 1);
+  const int64_t u0 = (int64_t)blockIdx.x * kEmitSpan;
+  const int64_t u1 = min(u0 + kEmitSpan, a.n_tok);
+  __shared__ int32_t start[65], dst[64], pos[64];
+  __shared__ uint8_t is_llm[64];
+  __shared__ int first;
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x < 64) {
+    const int b0 = wave_search(a.blk_start, u0, 0, a.n_blk - 1);
+    const int b = b0 + lane;
+    start[lane] = a.blk_start[min(b, a.n_blk)];                     // n_tok past the last
+    dst[lane] = b < a.n_blk ? a.dst_off[b] : -1;
+    pos[lane] = b < a.n_blk && dst[lane] >= 0 ? a.dst_pos[b] : 0;
+    is_llm[lane] = b < a.n_blk && llm_block(a, b);
+    if (lane == 0) {
+      start[64] = a.blk_start[min(b0 + 64, a.n_blk)];
+      first = b0;
+    }
   }
   __syncthreads();
-  const int64_t u = u0 + threadIdx.x;
-  if (u >= a.n_tok) return;
-  if ((a.flags[u] & AJ_AUTHOR_MASK) == AJ_AUTHOR_MASK) raise(a, AJ_DEVERR_BAD_FLAGS);
-  const int b = upper_index(a.blk_start, u, r[0], r[1]);
-  const int o0 = a.dst_off[b];
-  if (o0 < 0) return;
-  const int p = (int)(u - a.blk_start[b]);
-  const bool llm = llm_block(a, b);
-  a.otok[o0 + p] = a.tok[u];
-  a.opos[o0 + p] = a.dst_pos[b] + p;
-  a.omask[o0 + p] = llm;
-  a.olp[o0 + p] = llm ? a.old_logprob[u] : 0.f;
-  a.oadv[o0 + p] = llm ? a.adv[u] : 0.f;
+  const bool table = start[64] >= u1;
+  int bad = 0;
+  uint8_t f[kEmitPer];
+  int32_t o[kEmitPer], p[kEmitPer];     // destination and position, -1: nowhere
+  bool llm[kEmitPer];
+#pragma unroll
+  for (int r = 0; r < kEmitPer; ++r) {
+    const int64_t u = u0 + r * kBlock + threadIdx.x;
+    f[r] = a.flags[min(u, a.n_tok - 1)];
+  }
+#pragma unroll
+  for (int r = 0; r < kEmitPer; ++r) {
+    const int64_t u = u0 + r * kBlock + threadIdx.x;
+    o[r] = -1;
+    if (u >= u1) continue;
+    bad |= (f[r] & AJ_AUTHOR_MASK) == AJ_AUTHOR_MASK;
+    if (table) {
+      int k = 0;   // largest k with start[k] <= u
+#pragma unroll
+      for (int st = 32; st > 0; st >>= 1)
+        if (k + st < 64 && start[k + st] <= u) k += st;
+      if (dst[k] < 0) continue;
+      const int q = (int)(u - start[k]);
+      o[r] = dst[k] + q;
+      p[r] = pos[k] + q;
+      llm[r] = is_llm[k];
+    } else {
+      const int b = upper_index(a.blk_start, u, first, a.n_blk - 1);
+      const int d0 = a.dst_off[b];
+      if (d0 < 0) continue;
+      const int q = (int)(u - a.blk_start[b]);
+      o[r] = d0 + q;
+      p[r] = a.dst_pos[b] + q;
+      llm[r] = llm_block(a, b);
+    }
+  }
+  int32_t t[kEmitPer];
+  float lp[kEmitPer], ad[kEmitPer];
+#pragma unroll
+  for (int r = 0; r < kEmitPer; ++r) {   // issued together
+    const int64_t u = u0 + r * kBlock + threadIdx.x;
+    t[r] = 0;
+    lp[r] = ad[r] = 0.f;
+    if (o[r] >= 0) {
+      t[r] = a.tok[u];
+      if (llm[r]) {
+        lp[r] = a.old_logprob[u];
+        ad[r] = a.adv[u];
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < kEmitPer; ++r) {
+    if (o[r] < 0) continue;
+    a.otok[o[r]] = t[r];
+    a.opos[o[r]] = p[r];
+    a.omask[o[r]] = llm[r];
+    a.olp[o[r]] = lp[r];
+    a.oadv[o[r]] = ad[r];
+  }
+  if (bad) raise(a, AJ_DEVERR_BAD_FLAGS);
 }
 
-// One wavefront per block: an llm block of the output whose tokens before it
-// in its segment differ from those before it in its own timeline.
-__global__ __launch_bounds__(64) void ti_kernel(MergeArgs a) {
+// One workgroup per block: an llm block of the output whose tokens before it
+// in its segment differ from those before it in its own timeline.  2048 tokens a
+// step: a block late in a 30k-token segment took a lone wavefront (256 a step)
+// 120 dependent steps, 98 us; this takes 20.
+__global__ __launch_bounds__(kBlock) void ti_kernel(MergeArgs a) {
   const int b = blockIdx.x;
   if (fatal(a)) return;
   const int src = a.src_blk[b];
@@ -1349,15 +1428,20 @@ __global__ __launch_bounds__(64) void ti_kernel(MergeArgs a) {
   const int o0 = a.blk_off[a.tl_blk[a.blk_tl[b]]];
   const int64_t u1 = a.blk_start[src];
   const int64_t u0 = a.tl_tok_off[a.blk_tl[src]];
-  bool drift = (int64_t)(o1 - o0) != u1 - u0;
-  for (int64_t q0 = 0; !drift && q0 < o1 - o0; q0 += 64 * 4) {
-    bool bad = false;
+  const int n = o1 - o0;
+  int drift = (int64_t)n != u1 - u0;
+  for (int q0 = 0; !drift && q0 < n; q0 += 8 * kBlock) {
+    int32_t x[8], y[8];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t q = q0 + r * 64 + threadIdx.x;
-      if (q < o1 - o0) bad |= a.otok[o0 + q] != a.tok[u0 + q];
+    for (int r = 0; r < 8; ++r) {   // clamped (n >= 1): all loads issued together
+      const int q = min(q0 + r * kBlock + (int)threadIdx.x, n - 1);
+      x[r] = a.otok[o0 + q];
+      y[r] = a.tok[u0 + q];
     }
-    drift = __ballot(bad) != 0;
+    int bad = 0;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) bad |= x[r] != y[r];
+    drift = __syncthreads_or(bad);
   }
   if (drift && threadIdx.x == 0) {
     atomicAdd((unsigned long long *)&a.ti[0], 1ull);
@@ -1382,7 +1466,9 @@ struct MergeWs {
 MergeWs carve(void *ws, int32_t n_tl, int64_t n_tok, int32_t n_blk = -1) {
   aj::Carver c(ws);
   MergeWs w{};
-  int64_t n_chunks = (n_tok + kChunk - 1) / kChunk;
+  // target chunks; the block-start compaction's are longer
+  static_assert(kChunk >= kTgtChunk, "one array of counts for both");
+  int64_t n_chunks = (n_tok + kTgtChunk - 1) / kTgtChunk;
   auto at_least1 = [](int64_t n) { return n > 0 ? n : 1; };
   w.status = c.take<int32_t>(4);
   w.n_rblk = (int32_t)((n_tl + kResSpan - 1) / kResSpan);
@@ -1564,20 +1650,17 @@ int run_text(const aj_timelines *in, const aj_block_texts *text, aj_packed *out,
   if (in->n_tok > 0) blk_count_kernel<<<n_chunks, kBlock, 0, s>>>(a);
   blk_scan_kernel<<<1, 1024, 0, s>>>(a, (int)n_chunks);
   if (in->n_tok > 0) blk_write_kernel<<<n_chunks, kBlock, 0, s>>>(a);
-  tl_blk_kernel<<<(in->n_tl + 1 + kBlock - 1) / kBlock, kBlock, 0, s>>>(a);
-  if (n_blk > 0) blk_tl_kernel<<<gblk, kBlock, 0, s>>>(a);
+  const int n_tb = n_blk > in->n_tl + 1 ? n_blk : in->n_tl + 1;
+  tl_blk_kernel<<<(n_tb + kBlock - 1) / kBlock, kBlock, 0, s>>>(a);
   // Algorithm 1 in closed form on the keys, then the chosen blocks
   if (in->n_tl > 0) find_absorber_text_kernel<<<in->n_tl, 64, 0, s>>>(a);
-  if (n_blk > 0) {
-    claim_text_kernel<<<gblk, kBlock, 0, s>>>(a);
-    select_text_kernel<<<gblk, kBlock, 0, s>>>(a);
-  }
+  if (n_blk > 0) select_text_kernel<<<gblk, kBlock, 0, s>>>(a);
   resolve_text_kernel<<<1, 1024, 0, s>>>(a);
   if (n_blk > 0) place_text_kernel<<<gblk, kBlock, 0, s>>>(a);
   if (in->n_tok > 0)
-    emit_text_kernel<<<(in->n_tok + kBlock - 1) / kBlock, kBlock, 0, s>>>(a);
+    emit_text_kernel<<<(in->n_tok + kEmitSpan - 1) / kEmitSpan, kBlock, 0, s>>>(a);
   launch_targets(a, s, false);
-  if (ti && n_blk > 0) ti_kernel<<<n_blk, 64, 0, s>>>(a);
+  if (ti && n_blk > 0) ti_kernel<<<n_blk, kBlock, 0, s>>>(a);
   aj::timing_end(s, tk);
   return aj::check_launch(name);
 }
