@@ -143,12 +143,13 @@ size_t carve_lora_bwd(const aj_block_cfg &c, int r, int n, void *base, LoraBwd *
 
 // u of projection p from its input (row stride k_in).
 template <typename T>
-int lora_u(const aj_block_cfg &c, const LoraFwd &lf, int p, const T *in, int n, hipStream_t st) {
+int lora_u(const aj_block_cfg &c, const LoraFwd &lf, int p, const T *in, int n, const Saved &sv,
+           hipStream_t st) {
   using namespace aj;
   const int k_in = proj_in(c, p), r = lf.r;
   Gemm g;
   g.M = n; g.N = r; g.K = k_in; g.A = in; g.lda = k_in; g.B = lf.a[p]; g.ldb = k_in;
-  g.C = lf.u32; g.ldc = r; g.c_f32 = true;
+  g.C = lf.u32; g.ldc = r; g.c_f32 = true; g.partial = sv.part; g.partial_cap = sv.part_floats;
   if (int rc = gemm<T>(g, st)) return rc;
   scale_cast<T>(lf.u32, (int64_t)n * r, lf.scale, (T *)lf.u[p], nullptr, st);
   return AJ_OK;
@@ -177,6 +178,7 @@ int lora_grads(const aj_block_cfg &c, const LoraBwd &lb, int p, const T *d_out, 
   g = Gemm();   // v [n, r] = (d_out B)_s
   g.M = n; g.N = r; g.K = n_out; g.A = d_out; g.lda = n_out;
   g.B = lb.b[p]; g.ldb = r; g.b_kmajor = false; g.C = lb.v32; g.ldc = r; g.c_f32 = true;
+  g.partial = lb.partial; g.partial_cap = lb.partial_floats;
   if ((rc = gemm<T>(g, st))) return rc;
   scale_cast<T>(lb.v32, (int64_t)n * r, lb.scale, (T *)lb.vs, nullptr, st);
   g = Gemm();   // dA [r, k_in] += v^T in
@@ -236,7 +238,7 @@ int block_fwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   Gemm g;
   g.M = n; g.N = qdim; g.K = d;
   g.A = sv.a; g.lda = d; weight(g, w.w_qkv, w.w_qkv_t); g.C = sv.qkv; g.ldc = qdim;
-  if (lf && (r = lora_u<T>(c, *lf, kQkv, (const T *)sv.a, n, st))) return r;
+  if (lf && (r = lora_u<T>(c, *lf, kQkv, (const T *)sv.a, n, sv, st))) return r;
   lora_fwd_seg(g, lf, kQkv);
   if ((r = gemm<T>(g, st))) return r;
   rope<T>((T *)sv.qkv, n, v.pos, Hq + Hkv, qdim, hd, c.rope_theta, false, st);
@@ -246,7 +248,7 @@ int block_fwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   g = Gemm();
   g.M = n; g.N = d; g.K = Hq * hd;
   g.A = sv.o; g.lda = Hq * hd; weight(g, w.w_o, w.w_o_t); g.C = sv.x1; g.ldc = d; g.R = x;
-  if (lf && (r = lora_u<T>(c, *lf, kO, (const T *)sv.o, n, st))) return r;
+  if (lf && (r = lora_u<T>(c, *lf, kO, (const T *)sv.o, n, sv, st))) return r;
   lora_fwd_seg(g, lf, kO);
   if ((r = gemm<T>(g, st))) return r;
   rmsnorm_fwd<T>((const T *)sv.x1, (const T *)w.mlp_norm, n, d, c.rms_eps, nullptr, 0, (T *)sv.b,
@@ -254,14 +256,14 @@ int block_fwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   g = Gemm();
   g.M = n; g.N = 2 * F; g.K = d;
   g.A = sv.b; g.lda = d; weight(g, w.w_gate_up, w.w_gate_up_t); g.C = sv.gu; g.ldc = 2 * F;
-  if (lf && (r = lora_u<T>(c, *lf, kGu, (const T *)sv.b, n, st))) return r;
+  if (lf && (r = lora_u<T>(c, *lf, kGu, (const T *)sv.b, n, sv, st))) return r;
   lora_fwd_seg(g, lf, kGu);
   if ((r = gemm<T>(g, st))) return r;
   swiglu_fwd<T>((const T *)sv.gu, n, F, (T *)sv.s, st);
   g = Gemm();
   g.M = n; g.N = d; g.K = F;
   g.A = sv.s; g.lda = F; weight(g, w.w_down, w.w_down_t); g.C = y; g.ldc = d; g.R = sv.x1;
-  if (lf && (r = lora_u<T>(c, *lf, kDown, (const T *)sv.s, n, st))) return r;
+  if (lf && (r = lora_u<T>(c, *lf, kDown, (const T *)sv.s, n, sv, st))) return r;
   lora_fwd_seg(g, lf, kDown);
   if ((r = gemm<T>(g, st))) return r;
   return check_launch("aj_varlen_block_fwd");

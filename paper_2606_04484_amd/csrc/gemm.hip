@@ -203,8 +203,14 @@ AJ_DEV void gemm_tile(int M, int N, int K, const bf16_t *A, int64_t lda, const b
   const int lane = threadIdx.x & 63, wave = gemm_core::wave_id();
   const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
   f32x4_t acc[Cfg::TM][Cfg::TN];
-  gemm_core::mainloop<Cfg, A_K, B_K, SEG2>(acc, Seg{A, lda, B, ldb, kbeg, kend}, M, N, m0, n0, sm,
-                                           s2);
+  if constexpr (SEG2) {
+    // the second segment goes with the first piece
+    const Seg t2{s2.A, s2.lda, s2.B, s2.ldb, s2.kbeg, kbeg == 0 ? s2.kend : s2.kbeg};
+    gemm_core::mainloop<Cfg, A_K, B_K, true>(acc, Seg{A, lda, B, ldb, kbeg, kend}, M, N, m0, n0,
+                                             sm, t2);
+  } else {
+    gemm_core::mainloop<Cfg, A_K, B_K>(acc, Seg{A, lda, B, ldb, kbeg, kend}, M, N, m0, n0, sm);
+  }
   epi_barrier();
 
   // Epilogue through LDS, 32 rows of each wave row (two accumulator rows of
@@ -271,14 +277,14 @@ __global__ __launch_bounds__(Cfg::NT, Cfg::BM == 128 ? 2 : 1) void gemm_mfma_ker
   gemm_tile<A_K, B_K, Cfg>(M, N, K, A, lda, B, ldb, ep, pc, sm);
 }
 
-// The 8-wave kernel with a second reduction segment with the operand layouts of
-// the first, C = A B + A2 B2 (no split-K; used with either reduction length).
-template <bool A_K, bool B_K>
-__global__ __launch_bounds__(gemm_core::Cfg8::NT, 1) void gemm_mfma_seg2_kernel(
+// The same with a second reduction segment with the operand layouts of the
+// first, C = A B + A2 B2 (Cfg8 with either reduction length, or CfgS).
+template <typename Cfg, bool A_K, bool B_K>
+__global__ __launch_bounds__(Cfg::NT, Cfg::BM == 128 ? 2 : 1) void gemm_mfma_seg2_kernel(
     int M, int N, int K, const bf16_t *A, int64_t lda, const bf16_t *B, int64_t ldb, Seg s2,
     EpArgs ep, Pieces pc) {
-  __shared__ __attribute__((aligned(16))) gemm_core::Smem<gemm_core::Cfg8, A_K, B_K> sm;
-  gemm_tile<A_K, B_K, gemm_core::Cfg8, true>(M, N, K, A, lda, B, ldb, ep, pc, sm, s2);
+  __shared__ __attribute__((aligned(16))) gemm_core::Smem<Cfg, A_K, B_K> sm;
+  gemm_tile<A_K, B_K, Cfg, true>(M, N, K, A, lda, B, ldb, ep, pc, sm, s2);
 }
 
 // The pieces of each split tile added up in the order of their k ranges, then
@@ -443,8 +449,12 @@ void launch_mfma(const Gemm &g, const EpArgs &ep, const GemmPlan &pl, hipStream_
   const bf16_t *A = (const bf16_t *)g.A, *B = (const bf16_t *)g.B;
   if (g.K2 > 0) {
     const Seg s2{(const bf16_t *)g.A2, g.lda2, (const bf16_t *)g.B2, g.ldb2, 0, g.K2};
-    gemm_mfma_seg2_kernel<A_K, B_K><<<grid, gemm_core::Cfg8::NT, 0, s>>>(g.M, g.N, g.K, A, g.lda,
-                                                                       B, g.ldb, s2, ep, pc);
+    if (pl.tile == 128)
+      gemm_mfma_seg2_kernel<gemm_core::CfgS, A_K, B_K><<<grid, gemm_core::CfgS::NT, 0, s>>>(
+          g.M, g.N, g.K, A, g.lda, B, g.ldb, s2, ep, pc);
+    else
+      gemm_mfma_seg2_kernel<gemm_core::Cfg8, A_K, B_K><<<grid, gemm_core::Cfg8::NT, 0, s>>>(
+          g.M, g.N, g.K, A, g.lda, B, g.ldb, s2, ep, pc);
   } else if (pl.tile == 128) {
     gemm_mfma_kernel<gemm_core::CfgS, A_K, B_K><<<grid, gemm_core::CfgS::NT, 0, s>>>(
         g.M, g.N, g.K, A, g.lda, B, g.ldb, ep, pc);
@@ -493,10 +503,10 @@ static double rounds(int tile, int tiles, double k) {
 //   14500 x 1536, K 8960 (342 tiles): whole 376.8, last 86 in 2 pieces 312.2 us
 //   19437 x 3584, K 18944 (1064 tiles): whole 2140, last 40 in 6 pieces 1879 us
 //   700 x 17920, K 1536 (210 tiles): 256 whole 42.2, 128 whole 48.1 us
-GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool whole_only, bool swiglu) {
+GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool eight_wave) {
   auto tiles_of = [&](int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); };
-  GemmPlan best{256, K >= kLongK && !swiglu && !whole_only, tiles_of(256), tiles_of(256), 1, K};
-  if (whole_only || K <= 0) return best;
+  GemmPlan best{256, K >= kLongK && !eight_wave, tiles_of(256), tiles_of(256), 1, K};
+  if (K <= 0) return best;
   double t_best = rounds(256, best.tiles, K);
   for (int tile = 256; tile >= 128; tile /= 2) {
     const int tiles = tiles_of(tile);
@@ -515,7 +525,8 @@ GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool whole_only, boo
                        0.03 * pieces * tile * tile / 65536.0;
       if (t < t_best) {
         t_best = t;
-        best = {tile, tile == 256 && !swiglu && (whole ? K : k_piece) >= kLongK, tiles, whole, S, k_piece};
+        best = {tile, tile == 256 && !eight_wave && (whole ? K : k_piece) >= kLongK, tiles, whole, S,
+                k_piece};
       }
     }
   }
@@ -552,7 +563,7 @@ int gemm(const Gemm &g, hipStream_t s) {
   }
   const size_t cap = g.partial && aligned16(g.partial) ? g.partial_cap : 0;
   if (mfma) {
-    const GemmPlan pl = gemm_plan(g.M, g.N, g.K, cap, g.K2 > 0, g.swiglu_gu != nullptr);
+    const GemmPlan pl = gemm_plan(g.M, g.N, g.K, cap, g.K2 > 0 || g.swiglu_gu);
     int kc = g.a_kmajor ? (g.b_kmajor ? AJ_KC_GEMM_NT : AJ_KC_GEMM_NN) : AJ_KC_GEMM_TN;
     if (g.K >= kLongK && g.K2 == 0 && !g.swiglu_gu) kc += AJ_KC_GEMM4_NT - AJ_KC_GEMM_NT;
     const int tk =

@@ -63,7 +63,7 @@ struct Gemm {
   // at C[m][n] and d up = d s g sig(g) at C[m][F + n]
   const void *swiglu_gu = nullptr;
   bool recompute = false;      // recomputes a forward product: no algorithmic flops
-  // optional second reduction segment, same operand layouts, never split:
+  // optional second reduction segment, same operand layouts:
   // C (op) A B + A2 B2 with k in [0, K) and [0, K2)
   const void *A2 = nullptr; int64_t lda2 = 0;
   const void *B2 = nullptr; int64_t ldb2 = 0;
@@ -80,7 +80,7 @@ struct GemmPlan {
   bool long_k;          // 256: the 4-wave kernel
   int tiles, whole, split, k_piece;
 };
-GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool whole_only, bool swiglu);
+GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool eight_wave);
 
 constexpr int kMaxSplit = 16;
 // Scratch for the products of M x N outputs, in floats: every split stays
