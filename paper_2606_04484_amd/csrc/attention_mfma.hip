@@ -16,6 +16,7 @@
 // Query tiles are visited from the end of the pack (the longest rows first)
 // and the head index varies fastest, so the query heads that share a
 // key/value head run side by side.
+#include <algorithm>
 #include "ops.h"
 
 namespace aj {
@@ -605,9 +606,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_dq_mfma_kernel(AttnBwdArgs a,
 
 // ------------------------------------------------------------------ dK, dV
 // One workgroup: 32 * NW keys of one key/value head (NW waves of 32), a lane
-// owns one key; it walks every query head of the group and the segment's
-// query tiles of 64 after the keys (items), staged three deep (Q, dO and the
-// queries' LSE and delta) and shared by all the waves.
+// owns one key; it walks the query heads of the group (or of its part of them,
+// see dkv_parts) and the segment's query tiles of 64 after the keys (items),
+// staged three deep (Q, dO and the queries' LSE and delta) and shared by all
+// the waves.
 //
 // A lane holds its key's K and V rows and its dK, dV accumulators, which
 // leaves room for one wave per SIMD: nothing else on the SIMD covers the
@@ -691,7 +693,7 @@ struct DkvSched {
 };
 
 template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, int /*n_kt*/) {
+__global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, int parts) {
   using TT = TokTile<HD, NW>;
   constexpr int KS = HD / 16, DT = HD / 32, T = TT::kBytes, RB = HD * 2;
   constexpr int NS = 8 * DT, NC = NS / 2, D = 3;
@@ -707,7 +709,8 @@ __global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, i
   LQ.init(smq);
   LD.init(smd);
   const int t = work_item(blockIdx.x);
-  const int g = t % a.Hkv, kt = t / a.Hkv;   // early keys of a segment see the most queries
+  // early keys of a segment see the most queries
+  const int g = t % a.Hkv, part = t / a.Hkv % parts, kt = t / (a.Hkv * parts);
   const int ld = (a.Hq + 2 * a.Hkv) * HD;
   const int ldo = a.Hq * HD;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, hl = lane >> 5, lq = lane & 31;
@@ -750,13 +753,15 @@ __global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, i
   }
   __syncthreads();
   const int q_hi = rng[0];    // queries [k0, q_hi)
-  const int group = a.Hq / a.Hkv;
+  // the part's query heads [h0, h0 + n_h) of the group
+  const int group = a.Hq / a.Hkv, h_lo = group * part / parts, n_h = group * (part + 1) / parts - h_lo;
+  const int h0 = g * group + h_lo;
   const int n_qb = q_hi > k0 ? (q_hi - k0 + kTR - 1) / kTR : 0;
-  const int n_it = group * n_qb;
-  // item it: query head g*group + it / n_qb, query tile k0 + 64 * (it % n_qb)
+  const int n_it = n_h * n_qb;
+  // item it: query head h0 + it / n_qb, query tile k0 + 64 * (it % n_qb)
   auto load_item = [&](int it, auto ST) __attribute__((always_inline)) {
     constexpr int st = decltype(ST)::value;
-    const int h = g * group + it / n_qb, qb = k0 + kTR * (it % n_qb);
+    const int h = h0 + it / n_qb, qb = k0 + kTR * (it % n_qb);
     TT::load(smq + st * TT::kHalfs, qkv + h * HD, ld, qb, q_hi);
     TT::load(smd + st * TT::kHalfs, dout + h * HD, ldo, qb, q_hi);
     if (w < 2) {                // one float per lane: LSE (wave 0), delta (wave 1)
@@ -987,6 +992,20 @@ __global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, i
     tail(Ci<2>{});
   }
   if (!kvv) return;
+  if (parts > 1) {   // float32 sums of the part's heads, for attn_dkv_parts_kernel
+    float *p = a.part + ((int64_t)part * a.n_tok + kv) * (2 * a.Hkv * HD) + g * HD;
+#pragma unroll
+    for (int i = 0; i < DT; ++i)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const int d = 32 * i + 8 * r4 + 4 * hl;
+        *(f32x4_t *)(p + d) =
+            f32x4_t{dk[i][4 * r4], dk[i][4 * r4 + 1], dk[i][4 * r4 + 2], dk[i][4 * r4 + 3]};
+        *(f32x4_t *)(p + a.Hkv * HD + d) =
+            f32x4_t{dv[i][4 * r4], dv[i][4 * r4 + 1], dv[i][4 * r4 + 2], dv[i][4 * r4 + 3]};
+      }
+    return;
+  }
   bf16_t *base = (bf16_t *)a.dqkv + (int64_t)kv * ld;
 #pragma unroll
   for (int i = 0; i < DT; ++i)
@@ -999,6 +1018,21 @@ __global__ __launch_bounds__(64 * NW) void attn_dkv_mfma_kernel(AttnBwdArgs a, i
       *(u32x2_t *)(base + (a.Hq + a.Hkv + g) * HD + d) =
           u32x2_t{pack2(dv[i][4 * r4], dv[i][4 * r4 + 1]), pack2(dv[i][4 * r4 + 2], dv[i][4 * r4 + 3])};
     }
+}
+
+// dK, dV of the parts added up in their order, 4 features per thread
+__global__ __launch_bounds__(256) void attn_dkv_parts_kernel(AttnBwdArgs a, int parts) {
+  const int kw = a.Hkv * a.hd, w4 = kw / 2;   // 2 kw features of a row, in fours
+  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (int64_t)a.n_tok * w4) return;
+  const int64_t row = idx / w4;
+  const int col = (int)(idx % w4) * 4;
+  const float *p = a.part + row * (2 * kw) + col;
+  f32x4_t v = *(const f32x4_t *)p;
+  for (int z = 1; z < parts; ++z) v += *(const f32x4_t *)(p + (int64_t)z * a.n_tok * (2 * kw));
+  if (col < kw) v *= a.scale;
+  *(u32x2_t *)((bf16_t *)a.dqkv + row * (a.Hq + 2 * a.Hkv) * a.hd + a.Hq * a.hd + col) =
+      u32x2_t{pack2(v[0], v[1]), pack2(v[2], v[3])};
 }
 
 __global__ __launch_bounds__(256) void attn_delta_bf16_kernel(AttnBwdArgs a) {
@@ -1025,33 +1059,101 @@ bool attn_mfma_supported(int hd, const void *p0, const void *p1, const void *p2)
   return (hd == 64 || hd == 128) && aligned16(p0) && aligned16(p1) && aligned16(p2);
 }
 
-// Waves per workgroup: every wave of a workgroup shares each staged K/V
-// (forward, dQ) or Q/dO (dK/dV) tile.
-constexpr int kFwdWaves = 8, kDqWaves = 8, kDkvWaves = 4;
+// Waves per workgroup of the forward and dQ passes: every wave of a workgroup
+// shares each staged K/V tile.  Eight, unless there are no more such workgroups
+// than CUs (then four leave each wave a SIMD of its own) or the segments are
+// short (a workgroup of fewer rows reads fewer tiles that only some of its
+// waves use).  Forward, 8 waves against 4, us: one segment of 5000 tokens of 12
+// heads (240 workgroups) 148.1 / 134.0, two of 1173 44.3 / 36.4, four of 2000
+// of 28 heads 160.5 / 152.8, 40 of 1200 685 / 635; the other side: two of 3573
+// of 12 heads (336) 117.7 / 125.1, four of 3625 193.6 / 211.0, one of 45769 of
+// 40 heads 20340 / 21986.  dQ alike.  Two waves were never faster than the
+// better of these by more than 6 %, and up to 40 % slower.
+constexpr int kRowWaves = 8, kDkvWaves = 4;
+static bool few_rows(int n_tok, int n_seg, int heads) {
+  const int64_t wgs = (int64_t)((n_tok + 32 * kRowWaves - 1) / (32 * kRowWaves)) * heads;
+  return wgs <= 256 || (int64_t)n_seg * 2048 >= n_tok;
+}
+
+// In how many parts the dK/dV pass takes the query heads of a group.  Its
+// workgroups (128 keys of a KV head, every query head after them) are few and
+// uneven in a pack of moderate size, one to a CU: 228 of them for 14500 tokens
+// of 2 KV heads, whose time was that of the one with the most queries.  Parts
+// add float32 sums of their own per key, added up by a second kernel.
+// Predicted time in us of P parts: 1.9 us per (query head, query tile of 64)
+// at head_dim 128 and 5 per workgroup; the largest workgroup's while all run at
+// once, else an even share of the sum and part of the largest (one segment's
+// workgroups start heaviest first and leave a short tail); the sums' bytes.
+// Measured, in 1 part / in the parts chosen here, us:
+//   600 tokens of 12 heads, 2 KV 112 / 37 (6); 5000 of them 795 / 189 (6);
+//   4 segments of 3625 674 / 422 (6); 10 of 3000 906 / 741 (3);
+//   28 heads, 4 KV: 3000 558 / 177 (7); 4 of 2000 449 / 336 (4); 5 of 3887
+//   1477 / 1378 (4); 2 of 24000 17337 / 16990 (7)
+// and where one part is taken, 1 / as many as the group has heads:
+//   40 heads, 8 KV: 8000 1298 / 1406; 6 of 4000 2158 / 2445; 28 heads: 40 of
+//   1200 1199 / 1702.
+static int dkv_parts(const AttnBwdArgs &a) {
+  if (!a.part || !aligned16(a.part)) return 1;
+  const int group = a.Hq / a.Hkv;
+  const int64_t keys = ((int64_t)a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves) * a.Hkv;
+  const int64_t floats = (int64_t)a.n_tok * 2 * a.Hkv * a.hd;   // of a part's sums
+  const double tiles = (double)a.n_tok / a.n_seg / 64 + 1, tile = 1.9 * a.hd / 128;
+  auto time = [&](int P) {
+    const double top = tile * ((group + P - 1) / P) * tiles + 5, n = (double)keys * P;
+    const double even = (keys * group * tile * (tiles / 2 + 0.5) + n * 5) / 256;
+    const double t = n <= 256 ? top : std::max(top, even + (a.n_seg == 1 ? 0.1 : 0.6) * top);
+    return P == 1 ? t : t + 5 + 8.0 * P * floats / 7e6;
+  };
+  int best = 1;
+  double t_best = time(1);
+  for (int P = 2; P <= group && (size_t)(P * floats) <= a.part_floats; ++P)
+    if (time(P) < 0.98 * t_best) best = P, t_best = time(P);
+  return best;
+}
+
+template <int HD>
+static void launch_fwd(const AttnArgs &a, hipStream_t s) {
+  auto go = [&](auto W) {
+    constexpr int NW = decltype(W)::value;
+    const int n_qt = (a.n_tok + 32 * NW - 1) / (32 * NW);
+    attn_fwd_mfma_kernel<HD, NW><<<(unsigned)n_qt * a.Hq, 64 * NW, 0, s>>>(a, n_qt);
+  };
+  if (few_rows(a.n_tok, a.n_seg, a.Hq)) go(Ci<4>{});
+  else go(Ci<kRowWaves>{});
+}
 
 int attn_fwd_mfma(const AttnArgs &a, hipStream_t s) {
-  const int n_qt = (a.n_tok + 32 * kFwdWaves - 1) / (32 * kFwdWaves);
-  const unsigned grid = (unsigned)n_qt * a.Hq;
   const int tk = timing_begin(s, AJ_KC_ATTN_FWD, 0.0);
-  if (a.hd == 128) attn_fwd_mfma_kernel<128, kFwdWaves><<<grid, 64 * kFwdWaves, 0, s>>>(a, n_qt);
-  else attn_fwd_mfma_kernel<64, kFwdWaves><<<grid, 64 * kFwdWaves, 0, s>>>(a, n_qt);
+  if (a.hd == 128) launch_fwd<128>(a, s);
+  else launch_fwd<64>(a, s);
   timing_end(s, tk);
   return check_launch("attention forward (mfma)");
 }
 
+template <int HD>
+static void launch_bwd(const AttnBwdArgs &a, hipStream_t s) {
+  auto dq = [&](auto W) {
+    constexpr int NW = decltype(W)::value;
+    const int n_qt = (a.n_tok + 32 * NW - 1) / (32 * NW);
+    attn_dq_mfma_kernel<HD, NW><<<(unsigned)n_qt * a.Hq, 64 * NW, 0, s>>>(a, n_qt);
+  };
+  if (few_rows(a.n_tok, a.n_seg, a.Hq)) dq(Ci<4>{});
+  else dq(Ci<kRowWaves>{});
+  const int n_kt = (a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves), parts = dkv_parts(a);
+  attn_dkv_mfma_kernel<HD, kDkvWaves>
+      <<<(unsigned)n_kt * a.Hkv * parts, 64 * kDkvWaves, 0, s>>>(a, parts);
+  if (parts > 1) {
+    const int64_t n4 = (int64_t)a.n_tok * a.Hkv * (a.hd / 2);
+    attn_dkv_parts_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, s>>>(a, parts);
+  }
+}
+
 int attn_bwd_mfma(const AttnBwdArgs &a, hipStream_t s) {
-  const int n_qt = (a.n_tok + 32 * kDqWaves - 1) / (32 * kDqWaves);
-  const int n_kt = (a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves);
   const int64_t nd = (int64_t)a.n_tok * a.Hq;
   const int tk = timing_begin(s, AJ_KC_ATTN_BWD, 0.0);
   attn_delta_bf16_kernel<<<(unsigned)((nd + 3) / 4), 256, 0, s>>>(a);
-  if (a.hd == 128) {
-    attn_dq_mfma_kernel<128, kDqWaves><<<(unsigned)n_qt * a.Hq, 64 * kDqWaves, 0, s>>>(a, n_qt);
-    attn_dkv_mfma_kernel<128, kDkvWaves><<<(unsigned)n_kt * a.Hkv, 64 * kDkvWaves, 0, s>>>(a, n_kt);
-  } else {
-    attn_dq_mfma_kernel<64, kDqWaves><<<(unsigned)n_qt * a.Hq, 64 * kDqWaves, 0, s>>>(a, n_qt);
-    attn_dkv_mfma_kernel<64, kDkvWaves><<<(unsigned)n_kt * a.Hkv, 64 * kDkvWaves, 0, s>>>(a, n_kt);
-  }
+  if (a.hd == 128) launch_bwd<128>(a, s);
+  else launch_bwd<64>(a, s);
   timing_end(s, tk);
   return check_launch("attention backward (mfma)");
 }

@@ -344,6 +344,10 @@ int block_bwd(const aj_block_cfg &c, const aj_block_weights &w, const aj_varlen 
   if ((r = gemm<T>(g, st))) return r;
   AttnBwdArgs ab{n, v.n_seg, Hq, Hkv, hd, v.base, v.cu_seqlens, sv.qkv, sv.o, ws.dout, sv.lse,
                  ws.delta, ws.dqkv, 1.0f / sqrtf((float)hd)};
+  if constexpr (sizeof(T) == 2) {   // d gate / d up has been read: scratch
+    ab.part = (float *)ws.dgu;
+    ab.part_floats = (size_t)n * F;
+  }
   if ((r = attn_bwd<T>(ab, st))) return r;
   rope<T>((T *)ws.dqkv, n, v.pos, Hq + Hkv, qdim, hd, c.rope_theta, true, st);
   // qkv projection

@@ -123,6 +123,8 @@ struct AttnBwdArgs {
   float *delta;         // [Hq, n_tok] workspace
   void *dqkv;           // [n_tok, (Hq+2Hkv)*hd] written
   float scale;
+  float *part = nullptr;    // scratch for dK, dV in parts (16-byte aligned), part_floats of it
+  size_t part_floats = 0;
 };
 template <typename T>
 int attn_bwd(const AttnBwdArgs &a, hipStream_t s);

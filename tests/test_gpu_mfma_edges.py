@@ -109,3 +109,33 @@ def test_second_segment_steps(rank):
     np.testing.assert_allclose(a["lp"], b["lp"], atol=2e-2, rtol=0)
     for k, v in base.items():
         assert rel_l2(b["grads"][k][tuple(slice(0, s) for s in v.shape)], a["grads"][k]) <= 1e-2, k
+
+
+def test_second_segment_in_pieces():
+    """A down projection of 4104 features over few tokens runs in pieces, its
+    adapters' segment with the first of them: against the float64 oracle at the
+    bounds of the other bfloat16 actor tests (log-prob 2e-2, loss and gradients
+    1e-2, cosine 0.999)."""
+    import dataclasses
+    from tests.gpu_cases import Case, bf16_case_model, workload
+    from tests.test_gpu_actor import check, run_gpu
+    from workloads import make_lora_numpy
+    print("second segment in pieces", flush=True)
+    m = dataclasses.replace(bf16_case_model(hd=64, d=256, hq=4, hkv=2, ff=4104), n_layers=1)
+    case = Case(workload(m, n_traj=2), noise_std=0.3, margin=0.05,
+                lora=make_lora_numpy(m, 40, seed=2001, b_std=0.05), lora_scale=0.5)
+    check(case, run_gpu(case, True), True, 2e-2, 1e-2, 1e-2, 0.999)
+
+
+@pytest.mark.parametrize("hq,hkv,hd,ff", [(7, 1, 64, 128), (7, 1, 64, 512), (7, 1, 64, 1024),
+                                          (6, 2, 128, 1536), (4, 4, 128, 512)])
+def test_key_gradients_in_parts(hq, hkv, hd, ff):
+    """The dK/dV pass with a group's query heads in one part (128 and the group
+    of one head), in uneven ones (512: the scratch holds 4 parts of 7 heads) and
+    one head each: against the oracle at the same bounds."""
+    from tests.gpu_cases import Case, bf16_case_model, workload
+    from tests.test_gpu_actor import check, run_gpu
+    print(f"dK/dV parts hq={hq} hkv={hkv} hd={hd} ff={ff}", flush=True)
+    m = bf16_case_model(hd=hd, d=256, hq=hq, hkv=hkv, ff=ff)
+    case = Case(workload(m, n_traj=2), noise_std=0.3, margin=0.05)
+    check(case, run_gpu(case, True), True, 2e-2, 1e-2, 1e-2, 0.999)
