@@ -17,7 +17,8 @@
 // pass of dependent steps over a segment, which a wave per 16 rows (4 times the
 // rows in flight of a thread quad per row, and 16 of a step's keys at once)
 // shortens from 391 / 356 / 457 us (forward, dQ, dK and dV of 3443 tokens in 4
-// heads of 32) to 29 / 31 / 39.
+// heads of 32) to 29 / 31 / 39.  Loading a step's rows beside the step before and
+// splitting the score products' chain in two: 22 / 25 / 32.
 #include "ops.h"
 
 namespace aj {
@@ -61,26 +62,38 @@ template <int NC> constexpr int kLd = 16 * NC + 4;
 // Rows staged per step: 64, less where two such arrays would pass 64 KB.
 template <int NC> constexpr int kStep = NC <= 4 ? 64 : 32;
 
-// rows [r0, r0 + kStep) of a [rows, ld] matrix's hd columns into LDS (zeros past
-// `last` and past hd); hd is a multiple of 8, so four columns are in or out as one
+// The thread's share of rows [r0, r0 + kStep) of a [rows, ld] matrix's hd columns,
+// in fours (zeros past `last` and past hd; hd is a multiple of 8, so four columns
+// are in or out as one): loaded into registers, then put into LDS, so that a
+// step's loads run beside the step before.
+template <int NC> constexpr int kFours = kStep<NC> * NC * 4 / 256;
 template <typename T, int NC>
-AJ_DEV void stage_rows(float *lds, const T *p, int64_t ld, int hd, bool vec, int r0, int last) {
-  for (int e = threadIdx.x; e < kStep<NC> * NC * 4; e += 256) {
-    const int r = e / (NC * 4), c = e % (NC * 4) * 4;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+AJ_DEV void fetch_rows(float4 (&v)[kFours<NC>], const T *p, int64_t ld, int hd, bool vec, int r0,
+                       int last) {
+#pragma unroll
+  for (int q = 0; q < kFours<NC>; ++q) {
+    const int e = threadIdx.x + 256 * q, r = e / (NC * 4), c = e % (NC * 4) * 4;
+    v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (r0 + r <= last && c < hd) {
       const T *src = p + (int64_t)(r0 + r) * ld + c;
       if (vec && sizeof(T) == 4) {
-        v = *reinterpret_cast<const float4 *>(src);
+        v[q] = *reinterpret_cast<const float4 *>(src);
       } else if (vec) {
         const uint2 u = *reinterpret_cast<const uint2 *>(src);
-        v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
+        v[q] = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
+                           __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u));
       } else {
-        v = make_float4(ldf(src), ldf(src + 1), ldf(src + 2), ldf(src + 3));
+        v[q] = make_float4(ldf(src), ldf(src + 1), ldf(src + 2), ldf(src + 3));
       }
     }
-    *reinterpret_cast<float4 *>(lds + r * kLd<NC> + c) = v;
+  }
+}
+template <int NC>
+AJ_DEV void put_rows(float *lds, const float4 (&v)[kFours<NC>]) {
+#pragma unroll
+  for (int q = 0; q < kFours<NC>; ++q) {
+    const int e = threadIdx.x + 256 * q, r = e / (NC * 4), c = e % (NC * 4) * 4;
+    *reinterpret_cast<float4 *>(lds + r * kLd<NC> + c) = v[q];
   }
 }
 
@@ -112,14 +125,15 @@ AJ_DEV void store_row(T *p, const f32x4_t (&f)[NC], int hd, float scale) {
 template <int NC>
 AJ_DEV f32x4_t rows_dot(const float *rows, const f32x4_t (&own)[NC]) {
   const int lane = threadIdx.x & 63;
-  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+  // in two chains, which issue side by side
+  f32x4_t s[2] = {};
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const f32x4_t a = *reinterpret_cast<const f32x4_t *>(rows + (lane & 15) * kLd<NC> + 16 * c + 4 * (lane >> 4));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s = mfma4(a[j], own[c][j], s);
+    for (int j = 0; j < 4; ++j) s[j & 1] = mfma4(a[j], own[c][j], s[j & 1]);
   }
-  return s;
+  return s[0] + s[1];
 }
 // acc[features, lane's row] += sum over 16 rows of LDS, w[row] (the lane's rows
 // 4 (l/16) + j) times the row's features
@@ -127,9 +141,9 @@ template <int NC>
 AJ_DEV void rows_add(f32x4_t (&acc)[NC], const float *rows, const f32x4_t &w) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int c = 0; c < NC; ++c)
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int c = 0; c < NC; ++c)
       acc[c] = mfma4(rows[(4 * (lane >> 4) + j) * kLd<NC> + 16 * c + (lane & 15)], w[j], acc[c]);
 }
 
@@ -159,11 +173,18 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
   }
   float m = -INFINITY, l = 0.f;
   const int k_lo = seg_start(a, row0);
+  float4 kr[kFours<NC>], vr[kFours<NC>];
+  fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
+  fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
   for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
     __syncthreads();
-    stage_rows<T, NC>(Ks, kp, ld, hd, vec, k0, last);
-    stage_rows<T, NC>(Vs, vp, ld, hd, vec, k0, last);
+    put_rows<NC>(Ks, kr);
+    put_rows<NC>(Vs, vr);
     __syncthreads();
+    if (k0 + kStep<NC> <= last) {
+      fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
+      fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
+    }
     for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
       f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
       const int key = k0 + t + 4 * (lane >> 4);
@@ -238,11 +259,18 @@ __global__ __launch_bounds__(256) void attn_dq_f32_kernel(AttnBwdArgs a) {
 #pragma unroll
   for (int c = 0; c < NC; ++c) dq[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int k_lo = seg_start(a, row0);
+  float4 kr[kFours<NC>], vr[kFours<NC>];
+  fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
+  fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
   for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
     __syncthreads();
-    stage_rows<T, NC>(Ks, kp, ld, hd, vec, k0, last);
-    stage_rows<T, NC>(Vs, vp, ld, hd, vec, k0, last);
+    put_rows<NC>(Ks, kr);
+    put_rows<NC>(Vs, vr);
     __syncthreads();
+    if (k0 + kStep<NC> <= last) {
+      fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
+      fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
+    }
     for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
       const f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
       const f32x4_t dp = rows_dot<NC>(Vs + t * kLd<NC>, dob);
@@ -285,33 +313,43 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(AttnBwdArgs a) {
 #pragma unroll
   for (int c = 0; c < NC; ++c) dk[c] = dv[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int group = a.Hq / a.Hkv;
-  for (int hh = 0; hh < group; ++hh) {
-    const int h = g * group + hh;
-    for (int q0 = row0; q0 <= q_hi; q0 += kStep<NC>) {
-      __syncthreads();
-      stage_rows<T, NC>(Qs, qkv + h * hd, ld, hd, vec, q0, q_hi);
-      stage_rows<T, NC>(Ds, (const T *)a.dout + h * hd, (int64_t)a.Hq * hd, hd, vecd, q0, q_hi);
-      if ((int)threadIdx.x < kStep<NC>) {
-        const int qr = q0 + threadIdx.x;
-        Ls[threadIdx.x] = qr <= q_hi ? a.lse[(int64_t)h * a.n_tok + qr] : 0.f;
-        Dl[threadIdx.x] = qr <= q_hi ? a.delta[(int64_t)h * a.n_tok + qr] : 0.f;
-      }
-      __syncthreads();
-      for (int t = 0; t < kStep<NC> && q0 + t <= w_hi; t += 16) {
-        if (q0 + t + 15 < w0) continue;
-        const f32x4_t s = rows_dot<NC>(Qs + t * kLd<NC>, k);
-        const f32x4_t dp = rows_dot<NC>(Ds + t * kLd<NC>, v);
-        const int ql = t + 4 * (lane >> 4);
-        f32x4_t p, ds;
+  // the steps over every query head of the group, in one sequence
+  const int n_q = q_hi >= row0 ? (q_hi - row0) / kStep<NC> + 1 : 0;
+  float4 qr[kFours<NC>], dr[kFours<NC>];
+  float lr = 0.f, er = 0.f;
+  auto fetch = [&](int i) {
+    const int h = g * group + i / n_q, q0 = row0 + i % n_q * kStep<NC>;
+    fetch_rows<T, NC>(qr, qkv + h * hd, ld, hd, vec, q0, q_hi);
+    fetch_rows<T, NC>(dr, (const T *)a.dout + h * hd, (int64_t)a.Hq * hd, hd, vecd, q0, q_hi);
+    const int q = q0 + (int)threadIdx.x;
+    if ((int)threadIdx.x < kStep<NC>) {
+      lr = q <= q_hi ? a.lse[(int64_t)h * a.n_tok + q] : 0.f;
+      er = q <= q_hi ? a.delta[(int64_t)h * a.n_tok + q] : 0.f;
+    }
+  };
+  if (n_q > 0) fetch(0);
+  for (int i = 0; i < group * n_q; ++i) {
+    const int q0 = row0 + i % n_q * kStep<NC>;
+    __syncthreads();
+    put_rows<NC>(Qs, qr);
+    put_rows<NC>(Ds, dr);
+    if ((int)threadIdx.x < kStep<NC>) Ls[threadIdx.x] = lr, Dl[threadIdx.x] = er;
+    __syncthreads();
+    if (i + 1 < group * n_q) fetch(i + 1);
+    for (int t = 0; t < kStep<NC> && q0 + t <= w_hi; t += 16) {
+      if (q0 + t + 15 < w0) continue;
+      const f32x4_t s = rows_dot<NC>(Qs + t * kLd<NC>, k);
+      const f32x4_t dp = rows_dot<NC>(Ds + t * kLd<NC>, v);
+      const int ql = t + 4 * (lane >> 4);
+      f32x4_t p, ds;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const bool in = valid && q0 + ql + j >= row && q0 + ql + j < end;
-          p[j] = in ? __expf(s[j] * a.scale - Ls[ql + j]) : 0.f;
-          ds[j] = in ? p[j] * (dp[j] - Dl[ql + j]) * a.scale : 0.f;
-        }
-        rows_add<NC>(dv, Ds + t * kLd<NC>, p);
-        rows_add<NC>(dk, Qs + t * kLd<NC>, ds);
+      for (int j = 0; j < 4; ++j) {
+        const bool in = valid && q0 + ql + j >= row && q0 + ql + j < end;
+        p[j] = in ? __expf(s[j] * a.scale - Ls[ql + j]) : 0.f;
+        ds[j] = in ? p[j] * (dp[j] - Dl[ql + j]) * a.scale : 0.f;
       }
+      rows_add<NC>(dv, Ds + t * kLd<NC>, p);
+      rows_add<NC>(dk, Qs + t * kLd<NC>, ds);
     }
   }
   if (!valid) return;
