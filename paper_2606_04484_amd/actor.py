@@ -86,12 +86,17 @@ class Merger:
         cap = max(n_tok, 1)
         i32 = dict(dtype=torch.int32, device=dev)
         self.tl = tl_dev
+        # counts, cu_seqlens and cu_targets side by side: one copy brings them back
+        # (each row of offsets in whole 256-byte lines)
+        row = (n_tl + 1 + 63) // 64 * 64
+        self.head = torch.zeros(64 + 2 * row, **i32)
+        offs = self.head[64:].view(2, row)[:, :n_tl + 1]
         self.out = {
             "absorber": torch.empty(max(n_tl, 1), **i32),
-            "cu_seqlens": torch.empty(n_tl + 1, **i32),
+            "cu_seqlens": offs[0],
             "seg_src": torch.empty(max(n_tl, 1), **i32),
-            "cu_targets": torch.empty(n_tl + 1, **i32),
-            "counts": torch.zeros(4, dtype=torch.int64, device=dev),
+            "cu_targets": offs[1],
+            "counts": self.head[:8].view(torch.int64),
             "tok": torch.empty(cap, **i32),
             "pos": torch.empty(cap, **i32),
             "mask": torch.empty(cap, dtype=torch.uint8, device=dev),
@@ -100,12 +105,6 @@ class Merger:
             "targets": torch.empty(cap, **i32),
         }
         self.err = torch.zeros(1, **i32)
-        # pinned landing place of counts, cu_seqlens and cu_targets (see layout)
-        self.host = None
-        if n_tl <= self.ONE_COPY_TL:
-            pin = lambda n, dt: torch.empty(n, dtype=dt, pin_memory=dev.type == "cuda")
-            self.host = (pin(4, torch.int64), pin(n_tl + 1, torch.int32),
-                         pin(n_tl + 1, torch.int32))
         self.text = text
         if text:
             n_blk = tl_dev["blk_text"].numel()
@@ -129,13 +128,17 @@ class Merger:
         """Reads the counts and segment offsets back (one synchronisation for up to
         ONE_COPY_TL timelines) and plans the packs."""
         o = self.out
-        if self.host is not None:
-            src = (o["counts"], o["cu_seqlens"], o["cu_targets"])
-            for h, d in zip(self.host, src):
-                h.copy_(d, non_blocking=True)
-            torch.cuda.current_stream(o["counts"].device).synchronize()
-            n_seg, n_tok, n_mask, max_seqlen = self.host[0].tolist()
-            cu, cut = (h[:n_seg + 1].numpy().copy() for h in self.host[1:])
+        n_tl = o["cu_seqlens"].numel() - 1
+        if n_tl <= self.ONE_COPY_TL:
+            # into a pinned place of the call's own (torch's pool keeps it), so that
+            # several threads may read one merge
+            host = torch.empty(self.head.numel(), dtype=torch.int32, pin_memory=self.head.is_cuda)
+            host.copy_(self.head, non_blocking=True)
+            if self.head.is_cuda:
+                torch.cuda.current_stream(self.head.device).synchronize()
+            counts, offs = host[:8].view(torch.int64), host[64:].view(2, -1)
+            n_seg, n_tok, n_mask, max_seqlen = counts.tolist()
+            cu, cut = (h[:n_seg + 1].numpy().copy() for h in offs)
         else:
             n_seg, n_tok, n_mask, max_seqlen = (int(v) for v in o["counts"].cpu().tolist())
             cu = o["cu_seqlens"][:n_seg + 1].cpu().numpy()
