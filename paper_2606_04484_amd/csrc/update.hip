@@ -222,14 +222,16 @@ SelWs carve_sel(int n_traj, int n_tl, void *base) {
   return w;
 }
 
-// One item per thread: four consecutive parameters (VEC), the last n % 4 one
+// One item per thread: four consecutive parameters (VEC) and the last n % 4 one
 // each, or everything one each.  HBM-bound over seven streams (28 bytes a
 // parameter, 30 with a bfloat16 copy).  A grid-stride walk of 4096 workgroups
 // moved them at 4.8 TB/s; one item per thread 5.3, with non-temporal stores 5.4
 // and with non-temporal loads too 5.65 (513.5M parameters, 3.19 -> 2.73 ms).
-// The loads bypass the caches only where they could not stay there anyway: up to
-// kCached parameters the 16 bytes read of each fit the 256 MB last-level cache
-// (16M: 60 us against 81, 32M: 176 against 165).
+// Accesses bypass the caches only where the data could not stay there anyway: up
+// to kCached parameters the 16 bytes read of each fit the 256 MB last-level cache
+// (loads at 16M: 60 us against 81 non-temporal, at 32M 176 against 165; stores at
+// 2.5M: 9.7 against 11.0).  The last n % 4 have a loop of their own: as more items
+// of the first, 100000 parameters took 9.1 us instead of 8.6.
 constexpr int64_t kCached = 16 << 20;
 typedef float vf4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t vu2_t __attribute__((ext_vector_type(2)));
@@ -245,45 +247,51 @@ __global__ __launch_bounds__(256) void adamw_kernel(int64_t n, float *p, const f
     vv = b2 * vv + (1.f - b2) * gg * gg;
     pp = pp - lr * wd * pp - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
   };
-  const int64_t n4 = VEC ? n / 4 : 0;
+  const int64_t n4 = VEC ? n / 4 : 0, first = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n4 + (n - 4 * n4); t += stride) {
-    if (VEC && t < n4) {
-      auto load = [](const float *q, int64_t i) {
-        const vf4_t *a = reinterpret_cast<const vf4_t *>(q) + i;
-        return STREAM ? __builtin_nontemporal_load(a) : *a;
-      };
-      vf4_t pp = load(p, t), mm = load(m, t), vv = load(v, t);
+  if constexpr (VEC) {
+    auto load = [](const float *q, int64_t i) {
+      const vf4_t *a = reinterpret_cast<const vf4_t *>(q) + i;
+      if constexpr (STREAM) return __builtin_nontemporal_load(a);
+      else return *a;
+    };
+    auto store = [](auto *q, auto x) {
+      if constexpr (STREAM) __builtin_nontemporal_store(x, q);
+      else *q = x;
+    };
+    for (int64_t t = first; t < n4; t += stride) {
+      vf4_t pp = load(p, t);
       const vf4_t gg = load(g, t);
+      vf4_t mm = load(m, t), vv = load(v, t);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         float pe = pp[e], me = mm[e], ve = vv[e];
         one(pe, gg[e], me, ve);
         pp[e] = pe; mm[e] = me; vv[e] = ve;
       }
-      __builtin_nontemporal_store(pp, reinterpret_cast<vf4_t *>(p) + t);
-      __builtin_nontemporal_store(mm, reinterpret_cast<vf4_t *>(m) + t);
-      __builtin_nontemporal_store(vv, reinterpret_cast<vf4_t *>(v) + t);
+      store(reinterpret_cast<vf4_t *>(p) + t, pp);
+      store(reinterpret_cast<vf4_t *>(m) + t, mm);
+      store(reinterpret_cast<vf4_t *>(v) + t, vv);
       if (copy) {
         if constexpr (sizeof(TC) == 2)
-          __builtin_nontemporal_store(vu2_t{f2bf2(pp[0], pp[1]), f2bf2(pp[2], pp[3])},
-                                      reinterpret_cast<vu2_t *>(copy) + t);
+          store(reinterpret_cast<vu2_t *>(copy) + t, vu2_t{f2bf2(pp[0], pp[1]), f2bf2(pp[2], pp[3])});
         else
-          __builtin_nontemporal_store(pp, reinterpret_cast<vf4_t *>(copy) + t);
+          store(reinterpret_cast<vf4_t *>(copy) + t, pp);
       }
-    } else {
-      const int64_t i = 4 * n4 + (t - n4);
-      one(p[i], g[i], m[i], v[i]);
-      if (copy) stf(copy + i, p[i]);
     }
+  }
+  for (int64_t i = 4 * n4 + first; i < n; i += stride) {
+    one(p[i], g[i], m[i], v[i]);
+    if (copy) stf(copy + i, p[i]);
   }
 }
 
 template <typename TC>
 void adamw(int64_t n, float *p, const float *g, float *m, float *v, float lr, float b1, float b2,
            float eps, float wd, float c1, float c2, float gs, TC *copy, bool vec, hipStream_t st) {
-  const int64_t items = vec ? n / 4 + n % 4 : n, blocks = (items + 255) / 256;
-  const unsigned grid = (unsigned)(blocks < (1 << 30) ? blocks : (1 << 30));
+  const int64_t items = vec ? (n + 3) / 4 : n, blocks = (items + 255) / 256;
+  // a launch takes fewer than 2^32 threads: past that the walk strides
+  const unsigned grid = (unsigned)(blocks < (1 << 23) ? blocks : (1 << 23));
   if (vec && n > kCached)
     adamw_kernel<TC, true, true><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy);
   else if (vec)
