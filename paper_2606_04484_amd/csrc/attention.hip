@@ -19,6 +19,13 @@
 // shortens from 391 / 356 / 457 us (forward, dQ, dK and dV of 3443 tokens in 4
 // heads of 32) to 29 / 31 / 39.  Loading a step's rows beside the step before and
 // splitting the score products' chain in two: 22 / 25 / 32.
+//
+// A masked pair has weight 0 in those products, and 0 times an infinity or a NaN
+// is a NaN.  So a workgroup whose sums are not all finite takes its rows again,
+// with the masked pairs left out one by one: a bad row stays with the rows that
+// attend to it, and finite rows pay one check at the end (a check of every step's
+// rows cost 3 to 8 %).
+#include <type_traits>
 #include "ops.h"
 
 namespace aj {
@@ -136,15 +143,43 @@ AJ_DEV f32x4_t rows_dot(const float *rows, const f32x4_t (&own)[NC]) {
   return s[0] + s[1];
 }
 // acc[features, lane's row] += sum over 16 rows of LDS, w[row] (the lane's rows
-// 4 (l/16) + j) times the row's features
+// 4 (l/16) + j) times the row's features; w is 0 for rows without their bit in
+// `in`, which EXACT leaves out whatever they hold.
+template <bool EXACT, int NC>
+AJ_DEV void rows_add(f32x4_t (&acc)[NC], const float *rows, const f32x4_t &w, int in) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  if constexpr (EXACT) {
+    in <<= 4 * g;   // of the lane's column: all 16 rows
+    in |= __shfl_xor(in, 16, 64);
+    in |= __shfl_xor(in, 32, 64);
+#pragma unroll 1
+    for (int r = 0; r < 16; ++r) {
+      const float wj = r & 2 ? (r & 1 ? w[3] : w[2]) : (r & 1 ? w[1] : w[0]);
+      const float wr = __shfl(wj, (r >> 2) * 16 + col, 64);
+      if ((in >> r) & 1)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            acc[c][e] = fmaf(rows[r * kLd<NC> + 16 * c + 4 * g + e], wr, acc[c][e]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+        acc[c] = mfma4(rows[(4 * g + j) * kLd<NC> + 16 * c + col], w[j], acc[c]);
+  }
+}
+// Whether any thread's sums are not finite (in every thread of the workgroup).
 template <int NC>
-AJ_DEV void rows_add(f32x4_t (&acc)[NC], const float *rows, const f32x4_t &w) {
-  const int lane = threadIdx.x & 63;
+AJ_DEV bool any_nonfinite(const f32x4_t (&f)[NC], bool valid) {
+  f32x4_t z = {};
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-      acc[c] = mfma4(rows[(4 * (lane >> 4) + j) * kLd<NC> + 16 * c + (lane & 15)], w[j], acc[c]);
+    for (int e = 0; e < 4; ++e) z[e] = fmaf(f[c][e], 0.f, z[e]);
+  return __syncthreads_or(valid && !(z[0] + z[1] + z[2] + z[3] == 0.f));
 }
 
 AJ_DEV bool vec4(const void *p, int64_t ld, int es) {
@@ -166,54 +201,62 @@ __global__ __launch_bounds__(256) void attn_fwd_f32_kernel(AttnArgs a) {
   f32x4_t q[NC], o[NC];
   own_row<T, NC>(q, qkv + (int64_t)row * ld + h * hd, hd, valid);
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
+  for (int c = 0; c < NC; ++c)
 #pragma unroll
     for (int j = 0; j < 4; ++j) q[c][j] *= a.scale;
-    o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
-  float m = -INFINITY, l = 0.f;
+  float m, l;
   const int k_lo = seg_start(a, row0);
   float4 kr[kFours<NC>], vr[kFours<NC>];
-  fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
-  fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
-  for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
-    __syncthreads();
-    put_rows<NC>(Ks, kr);
-    put_rows<NC>(Vs, vr);
-    __syncthreads();
-    if (k0 + kStep<NC> <= last) {
-      fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
-      fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
-    }
-    for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
-      f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
-      const int key = k0 + t + 4 * (lane >> 4);
-      float mx = -INFINITY;
+  auto walk = [&](auto exact) __attribute__((always_inline)) {
+    m = -INFINITY;
+    l = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (key + j < start || key + j > row || !valid) s[j] = -INFINITY;
-        mx = fmaxf(mx, s[j]);
+    for (int c = 0; c < NC; ++c) o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
+    fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
+    for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
+      __syncthreads();
+      put_rows<NC>(Ks, kr);
+      put_rows<NC>(Vs, vr);
+      __syncthreads();
+      if (k0 + kStep<NC> <= last) {
+        fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
+        fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mn = fmaxf(m, mx);
-      // a query that has seen no key yet keeps zero weights (mn is -inf)
-      const float sc = mn == -INFINITY ? 1.f : __expf(m - mn);
-      float sum = 0.f;
+      for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
+        f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
+        const int key = k0 + t + 4 * (lane >> 4);
+        float mx = -INFINITY;
+        int in = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        s[j] = s[j] == -INFINITY ? 0.f : __expf(s[j] - mn);
-        sum += s[j];
+        for (int j = 0; j < 4; ++j) {
+          if (key + j < start || key + j > row || !valid) s[j] = -INFINITY;
+          else in |= 1 << j;
+          mx = fmaxf(mx, s[j]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float mn = fmaxf(m, mx);
+        // a query that has seen no key yet keeps zero weights (mn is -inf)
+        const float sc = mn == -INFINITY ? 1.f : __expf(m - mn);
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          s[j] = s[j] == -INFINITY ? 0.f : __expf(s[j] - mn);
+          sum += s[j];
+        }
+        l = l * sc + sum;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) o[c][j] *= sc;
+        rows_add<decltype(exact)::value>(o, Vs + t * kLd<NC>, s, in);
+        m = mn;
       }
-      l = l * sc + sum;
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o[c][j] *= sc;
-      rows_add<NC>(o, Vs + t * kLd<NC>, s);
-      m = mn;
     }
-  }
+  };
+  walk(std::false_type{});
+  if (any_nonfinite<NC>(o, valid)) walk(std::true_type{});
   // each lane has summed its own keys' weights
   l += __shfl_xor(l, 16, 64);
   l += __shfl_xor(l, 32, 64);
@@ -256,34 +299,40 @@ __global__ __launch_bounds__(256) void attn_dq_f32_kernel(AttnBwdArgs a) {
   f32x4_t q[NC], dob[NC], dq[NC];
   own_row<T, NC>(q, qkv + (int64_t)row * ld + h * hd, hd, valid);
   own_row<T, NC>(dob, (const T *)a.dout + (int64_t)row * a.Hq * hd + h * hd, hd, valid);
-#pragma unroll
-  for (int c = 0; c < NC; ++c) dq[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int k_lo = seg_start(a, row0);
   float4 kr[kFours<NC>], vr[kFours<NC>];
-  fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
-  fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
-  for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
-    __syncthreads();
-    put_rows<NC>(Ks, kr);
-    put_rows<NC>(Vs, vr);
-    __syncthreads();
-    if (k0 + kStep<NC> <= last) {
-      fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
-      fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
-    }
-    for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
-      const f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
-      const f32x4_t dp = rows_dot<NC>(Vs + t * kLd<NC>, dob);
-      const int key = k0 + t + 4 * (lane >> 4);
-      f32x4_t ds;
+  auto walk = [&](auto exact) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool in = valid && key + j >= start && key + j <= row;
-        ds[j] = in ? __expf(s[j] * a.scale - lse) * (dp[j] - delta) * a.scale : 0.f;
+    for (int c = 0; c < NC; ++c) dq[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    fetch_rows<T, NC>(kr, kp, ld, hd, vec, k_lo, last);
+    fetch_rows<T, NC>(vr, vp, ld, hd, vec, k_lo, last);
+    for (int k0 = k_lo; k0 <= last; k0 += kStep<NC>) {
+      __syncthreads();
+      put_rows<NC>(Ks, kr);
+      put_rows<NC>(Vs, vr);
+      __syncthreads();
+      if (k0 + kStep<NC> <= last) {
+        fetch_rows<T, NC>(kr, kp, ld, hd, vec, k0 + kStep<NC>, last);
+        fetch_rows<T, NC>(vr, vp, ld, hd, vec, k0 + kStep<NC>, last);
       }
-      rows_add<NC>(dq, Ks + t * kLd<NC>, ds);
+      for (int t = 0; t < kStep<NC> && k0 + t <= w0 + 15; t += 16) {
+        const f32x4_t s = rows_dot<NC>(Ks + t * kLd<NC>, q);
+        const f32x4_t dp = rows_dot<NC>(Vs + t * kLd<NC>, dob);
+        const int key = k0 + t + 4 * (lane >> 4);
+        f32x4_t ds;
+        int in = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool inj = valid && key + j >= start && key + j <= row;
+          ds[j] = inj ? __expf(s[j] * a.scale - lse) * (dp[j] - delta) * a.scale : 0.f;
+          in |= inj << j;
+        }
+        rows_add<decltype(exact)::value>(dq, Ks + t * kLd<NC>, ds, in);
+      }
     }
-  }
+  };
+  walk(std::false_type{});
+  if (any_nonfinite<NC>(dq, valid)) walk(std::true_type{});
   if (valid) store_row<T, NC>((T *)a.dqkv + (int64_t)row * ld + h * hd, dq, hd, 1.f);
 }
 
@@ -310,8 +359,6 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(AttnBwdArgs a) {
   f32x4_t k[NC], v[NC], dk[NC], dv[NC];
   own_row<T, NC>(k, qkv + (int64_t)row * ld + (a.Hq + g) * hd, hd, valid);
   own_row<T, NC>(v, qkv + (int64_t)row * ld + (a.Hq + a.Hkv + g) * hd, hd, valid);
-#pragma unroll
-  for (int c = 0; c < NC; ++c) dk[c] = dv[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int group = a.Hq / a.Hkv;
   // the steps over every query head of the group, in one sequence
   const int n_q = q_hi >= row0 ? (q_hi - row0) / kStep<NC> + 1 : 0;
@@ -327,31 +374,40 @@ __global__ __launch_bounds__(256) void attn_dkv_f32_kernel(AttnBwdArgs a) {
       er = q <= q_hi ? a.delta[(int64_t)h * a.n_tok + q] : 0.f;
     }
   };
-  if (n_q > 0) fetch(0);
-  for (int i = 0; i < group * n_q; ++i) {
-    const int q0 = row0 + i % n_q * kStep<NC>;
-    __syncthreads();
-    put_rows<NC>(Qs, qr);
-    put_rows<NC>(Ds, dr);
-    if ((int)threadIdx.x < kStep<NC>) Ls[threadIdx.x] = lr, Dl[threadIdx.x] = er;
-    __syncthreads();
-    if (i + 1 < group * n_q) fetch(i + 1);
-    for (int t = 0; t < kStep<NC> && q0 + t <= w_hi; t += 16) {
-      if (q0 + t + 15 < w0) continue;
-      const f32x4_t s = rows_dot<NC>(Qs + t * kLd<NC>, k);
-      const f32x4_t dp = rows_dot<NC>(Ds + t * kLd<NC>, v);
-      const int ql = t + 4 * (lane >> 4);
-      f32x4_t p, ds;
+  auto walk = [&](auto exact) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool in = valid && q0 + ql + j >= row && q0 + ql + j < end;
-        p[j] = in ? __expf(s[j] * a.scale - Ls[ql + j]) : 0.f;
-        ds[j] = in ? p[j] * (dp[j] - Dl[ql + j]) * a.scale : 0.f;
+    for (int c = 0; c < NC; ++c) dk[c] = dv[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (n_q > 0) fetch(0);
+    for (int i = 0; i < group * n_q; ++i) {
+      const int q0 = row0 + i % n_q * kStep<NC>;
+      __syncthreads();
+      put_rows<NC>(Qs, qr);
+      put_rows<NC>(Ds, dr);
+      if ((int)threadIdx.x < kStep<NC>) Ls[threadIdx.x] = lr, Dl[threadIdx.x] = er;
+      __syncthreads();
+      if (i + 1 < group * n_q) fetch(i + 1);
+      for (int t = 0; t < kStep<NC> && q0 + t <= w_hi; t += 16) {
+        if (q0 + t + 15 < w0) continue;
+        const f32x4_t s = rows_dot<NC>(Qs + t * kLd<NC>, k);
+        const f32x4_t dp = rows_dot<NC>(Ds + t * kLd<NC>, v);
+        const int ql = t + 4 * (lane >> 4);
+        f32x4_t p, ds;
+        int in = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool inj = valid && q0 + ql + j >= row && q0 + ql + j < end;
+          p[j] = inj ? __expf(s[j] * a.scale - Ls[ql + j]) : 0.f;
+          ds[j] = inj ? p[j] * (dp[j] - Dl[ql + j]) * a.scale : 0.f;
+          in |= inj << j;
+        }
+        rows_add<decltype(exact)::value>(dv, Ds + t * kLd<NC>, p, in);
+        rows_add<decltype(exact)::value>(dk, Qs + t * kLd<NC>, ds, in);
       }
-      rows_add<NC>(dv, Ds + t * kLd<NC>, p);
-      rows_add<NC>(dk, Qs + t * kLd<NC>, ds);
     }
-  }
+  };
+  walk(std::false_type{});
+  // not `||`: every thread takes both barriers
+  if (any_nonfinite<NC>(dk, valid) | any_nonfinite<NC>(dv, valid)) walk(std::true_type{});
   if (!valid) return;
   T *base = (T *)a.dqkv + (int64_t)row * ld;
   store_row<T, NC>(base + (a.Hq + g) * hd, dk, hd, 1.f);
