@@ -241,11 +241,14 @@ __global__ __launch_bounds__(256) void adamw_kernel(int64_t n, float *p, const f
                                                     float *v, float lr, float b1, float b2,
                                                     float eps, float wd, float c1, float c2,
                                                     float gs, TC *copy) {
+  // m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2, p -= lr (wd p + (m / c1) /
+  // (sqrt(v / c2) + eps)); which product of a sum is fused into it is stated, so
+  // that every form of the loop gives the same bits
   auto one = [&](float &pp, float gg, float &mm, float &vv) {
     gg *= gs;
-    mm = b1 * mm + (1.f - b1) * gg;
-    vv = b2 * vv + (1.f - b2) * gg * gg;
-    pp = pp - lr * wd * pp - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
+    mm = fmaf(1.f - b1, gg, b1 * mm);
+    vv = fmaf((1.f - b2) * gg, gg, b2 * vv);
+    pp = fmaf(-(lr * wd), pp, pp) - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
   };
   const int64_t n4 = VEC ? n / 4 : 0, first = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * 256;

@@ -10,6 +10,9 @@
   parameter count of the 1.5B-class workload (block + embedding + LM head,
   ~513M values) on sampled elements.
 """
+import ctypes
+import ctypes.util
+
 import numpy as np
 import pytest
 import torch
@@ -218,3 +221,45 @@ def test_adamw_either_side_of_the_cached_size(extra, copy):
     torch.cuda.synchronize()
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+def _adamw_bits(p, g, m, v, lr, b1, b2, eps, wd, step, gs):
+    """One AdamW step in float32, operation by operation as the kernel states it."""
+    f = np.float32
+    libm = ctypes.CDLL(ctypes.util.find_library("m"))
+    for name, n in (("fmaf", 3), ("powf", 2)):
+        getattr(libm, name).argtypes, getattr(libm, name).restype = [ctypes.c_float] * n, ctypes.c_float
+    fma = np.vectorize(lambda a, b, c: libm.fmaf(a, b, c), otypes=[f])
+    lr, b1, b2, eps, wd, gs = (f(t) for t in (lr, b1, b2, eps, wd, gs))
+    c1, c2 = (f(1) - f(libm.powf(b, step)) for b in (b1, b2))
+    g = g * gs
+    m = fma(f(1) - b1, g, b1 * m)
+    v = fma((f(1) - b2) * g, g, b2 * v)
+    p = fma(-(lr * wd), p, p) - lr * (m / c1) / (np.sqrt(v / c2) + eps)
+    return p, m, v
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2])
+@pytest.mark.parametrize("copy", [None, torch.float32, torch.bfloat16])
+def test_adamw_bits(copy, offset):
+    """Every form of the kernel (four parameters a thread, one, the last n % 4) does
+    the same operations in the same order: bits equal to the host's float32."""
+    from paper_2606_04484_amd import capi
+    n = 4099
+    rng = np.random.default_rng(5 + offset)
+    host = [(rng.standard_normal(n) * s).astype(np.float32) for s in (0.02, 1e-3, 1e-4, 1e-6)]
+    host[3] = np.abs(host[3])
+    hp = (2e-4, 0.9, 0.95, 1e-8, 0.1, 3)
+    dev = []
+    for k, h in enumerate(host):
+        t = torch.zeros(n + 4, device="cuda")[offset:offset + n]
+        t.copy_(torch.from_numpy(h))
+        dev.append(t)
+    c = None if copy is None else torch.zeros(n + 4, dtype=copy, device="cuda")[offset:offset + n]
+    print(f"adamw bits offset={offset} copy={copy}", flush=True)
+    capi.aj_adamw_step(*dev, *hp, grad_scale=0.37, param_copy=c)
+    ref = _adamw_bits(*host, *hp, 0.37)
+    for got, want in zip((dev[0], dev[2], dev[3]), ref):
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+    if c is not None:
+        assert torch.equal(c.cpu(), torch.from_numpy(ref[0]).to(copy))
