@@ -234,13 +234,23 @@ SelWs carve_sel(int n_traj, int n_tl, void *base) {
 // of the first, 100000 parameters took 9.1 us instead of 8.6.
 constexpr int64_t kCached = 16 << 20;
 typedef float vf4_t __attribute__((ext_vector_type(4)));
+typedef float vf2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t vu2_t __attribute__((ext_vector_type(2)));
+
+bool aligned(const void *p, int bytes) { return ((uintptr_t)p & (bytes - 1)) == 0; }
+
+// Four parameters a thread: 16-byte accesses of the four arrays; the copy (if any)
+// in 8-byte pieces at least, which a float32 one at 8 bytes takes two of (16M
+// parameters: 76 us, 103 with one parameter a thread).
+bool adamw_vec(const void *p, const void *g, const void *m, const void *v, const void *copy) {
+  return aligned(p, 16) && aligned(g, 16) && aligned(m, 16) && aligned(v, 16) && aligned(copy, 8);
+}
 
 template <typename TC, bool VEC, bool STREAM>
 __global__ __launch_bounds__(256) void adamw_kernel(int64_t n, float *p, const float *g, float *m,
                                                     float *v, float lr, float b1, float b2,
                                                     float eps, float wd, float c1, float c2,
-                                                    float gs, TC *copy) {
+                                                    float gs, TC *copy, bool copy16) {
   // m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2, p -= lr (wd p + (m / c1) /
   // (sqrt(v / c2) + eps)); which product of a sum is fused into it is stated, so
   // that every form of the loop gives the same bits
@@ -276,10 +286,14 @@ __global__ __launch_bounds__(256) void adamw_kernel(int64_t n, float *p, const f
       store(reinterpret_cast<vf4_t *>(m) + t, mm);
       store(reinterpret_cast<vf4_t *>(v) + t, vv);
       if (copy) {
-        if constexpr (sizeof(TC) == 2)
+        if constexpr (sizeof(TC) == 2) {
           store(reinterpret_cast<vu2_t *>(copy) + t, vu2_t{f2bf2(pp[0], pp[1]), f2bf2(pp[2], pp[3])});
-        else
+        } else if (copy16) {
           store(reinterpret_cast<vf4_t *>(copy) + t, pp);
+        } else {
+          store(reinterpret_cast<vf2_t *>(copy) + 2 * t, vf2_t{pp[0], pp[1]});
+          store(reinterpret_cast<vf2_t *>(copy) + 2 * t + 1, vf2_t{pp[2], pp[3]});
+        }
       }
     }
   }
@@ -292,18 +306,17 @@ __global__ __launch_bounds__(256) void adamw_kernel(int64_t n, float *p, const f
 template <typename TC>
 void adamw(int64_t n, float *p, const float *g, float *m, float *v, float lr, float b1, float b2,
            float eps, float wd, float c1, float c2, float gs, TC *copy, bool vec, hipStream_t st) {
+  const bool copy16 = aligned(copy, 16);
   const int64_t items = vec ? (n + 3) / 4 : n, blocks = (items + 255) / 256;
   // a launch takes fewer than 2^32 threads: past that the walk strides
   const unsigned grid = (unsigned)(blocks < (1 << 23) ? blocks : (1 << 23));
   if (vec && n > kCached)
-    adamw_kernel<TC, true, true><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy);
+    adamw_kernel<TC, true, true><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy, copy16);
   else if (vec)
-    adamw_kernel<TC, true, false><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy);
+    adamw_kernel<TC, true, false><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy, copy16);
   else
-    adamw_kernel<TC, false, false><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy);
+    adamw_kernel<TC, false, false><<<grid, 256, 0, st>>>(n, p, g, m, v, lr, b1, b2, eps, wd, c1, c2, gs, copy, copy16);
 }
-
-bool al16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 }  // namespace
 
@@ -376,8 +389,7 @@ extern "C" int aj_adamw_step(int64_t n, float *param, const float *grad, float *
   hipStream_t st = (hipStream_t)stream;
   const float c1 = 1.f - powf(beta1, (float)step), c2 = 1.f - powf(beta2, (float)step);
   const bool bf16 = copy_dtype == AJ_BF16;
-  const bool vec = al16(param) && al16(grad) && al16(m) && al16(v) &&
-                   ((uintptr_t)param_copy & (bf16 ? 7 : 15)) == 0;
+  const bool vec = adamw_vec(param, grad, m, v, param_copy);
   const int tk = aj::timing_begin(st, AJ_KC_ADAMW, 0.0);
   if (bf16)
     adamw<bf16_t>(n, param, grad, m, v, lr, beta1, beta2, eps, weight_decay, c1, c2, grad_scale,
