@@ -264,7 +264,10 @@ __global__ __launch_bounds__(256) void embed_tile_kernel(const uint64_t *keys, i
 }
 
 // Step 3: the run crossing boundary b = (blockIdx.x + 1) * kTile, if it
-// crosses no earlier boundary; one thread per 4 columns.
+// crosses no earlier boundary; one thread per 4 columns.  A run may span every
+// tile: eight of its pieces are loaded at a time, added in order (one at a time, a
+// load behind each token check, 65535 rows of one token and 128 columns took 321
+// us in all).
 template <int kTile>
 __global__ __launch_bounds__(256) void embed_cross_kernel(const uint64_t *keys, int n, int n_tiles,
                                                           int d, const float *piece, float *demb) {
@@ -277,10 +280,21 @@ __global__ __launch_bounds__(256) void embed_cross_kernel(const uint64_t *keys, 
   const int col0 = (blockIdx.y * 256 + threadIdx.x) * 4;
   if (col0 >= d) return;
   float4 acc = *(const float4 *)(piece + ((int64_t)(bt - 1) * 2 + 1) * d + col0);
-  for (int u = bt;; ++u) {
-    add4(acc, *(const float4 *)(piece + ((int64_t)u * 2) * d + col0));
-    const int64_t e = (int64_t)(u + 1) * kTile;
-    if (u + 1 >= n_tiles || e >= n || key_tok(keys[e]) != t) break;
+  // the run's later tiles [bt, end): those that begin with its token (sorted keys)
+  int end = bt + 1, hi = n_tiles;
+  while (end < hi) {
+    const int mid = (end + hi) >> 1;
+    if (key_tok(keys[(int64_t)mid * kTile]) == t) end = mid + 1; else hi = mid;
+  }
+  for (int u = bt; u < end; u += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      v[q] = u + q < end ? *(const float4 *)(piece + ((int64_t)(u + q) * 2) * d + col0)
+                         : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (u + q < end) add4(acc, v[q]);
   }
   float4 *o = (float4 *)(demb + (int64_t)t * d + col0);
   float4 v = *o;

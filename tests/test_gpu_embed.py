@@ -139,3 +139,52 @@ def test_embed_fwd_widths(d, dtype):
     capi.aj_embed_fwd(tok, emb, x, None)
     ok = ((tok >= 0) & (tok < 50)).unsqueeze(1)
     assert torch.equal(x, torch.where(ok, emb[tok.clamp(0, 49).long()], torch.zeros((), dtype=dtype, device="cuda")))
+
+
+@pytest.mark.parametrize("n", [64 * 9, 64 * 9 + 1, 64 * 17 + 5, 65535, 256 * 300])
+def test_embed_bwd_runs_over_many_tiles(n):
+    """One token in all but a few rows: the run's pieces come from 8 tiles and fewer,
+    one more, and hundreds, of both tile sizes; the sum order is a float32 chain over
+    256 rows or fewer and then over the tiles (1e-5 of the sum of magnitudes)."""
+    from paper_2606_04484_amd import capi
+    rng = np.random.default_rng(n)
+    print(f"embed run n={n}", flush=True)
+    tok = np.full(n, 5, np.int32)
+    tok[rng.integers(0, n, 7)] = rng.integers(0, 20, 7)
+    dx = rng.standard_normal((n, 8)).astype(np.float32)
+    outs = []
+    for _ in range(2):
+        g = torch.zeros(20, 8, device="cuda")
+        _bwd(capi, torch.from_numpy(tok).cuda(), torch.from_numpy(dx).cuda(), g)
+        outs.append(g.cpu().numpy())
+    assert np.array_equal(outs[0], outs[1])
+    ref, scale = np.zeros((20, 8)), np.zeros((20, 8))
+    np.add.at(ref, tok, dx.astype(np.float64))
+    np.add.at(scale, tok, np.abs(dx).astype(np.float64))
+    assert np.max(np.abs(outs[0] - ref) / (scale + 1e-30)) <= 1e-5
+
+
+def test_embed_bwd_one_run_is_no_serial_chain():
+    """65535 rows of one token take no more than 4 times those of spread tokens (2.3
+    measured; 6 with the run's 1024 pieces loaded one after another)."""
+    from paper_2606_04484_amd import capi
+    n, d, vocab = 65535, 128, 30000
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    spread = torch.randint(0, vocab, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    one = torch.full_like(spread, 7)
+    dx, de = torch.randn(n, d, generator=gen, device="cuda"), torch.zeros(vocab, d, device="cuda")
+    ws = torch.empty(capi.aj_embed_bwd_workspace_bytes(n, d), dtype=torch.uint8, device="cuda")
+    best = []
+    for tok in (spread, one):
+        t = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                capi.aj_embed_bwd(tok, dx, de, ws)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b))
+        best.append(min(t))
+    print(f"spread {best[0] * 100:.1f} us, one token {best[1] * 100:.1f} us", flush=True)
+    assert best[1] <= 4 * best[0]
