@@ -32,6 +32,12 @@ constexpr int kSmallRows = 65536;
 int tile_rows(int n) { return n < kSmallRows ? 64 : 256; }
 int64_t n_tiles(int n) { return (n + tile_rows(n) - 1) / tile_rows(n); }
 
+// The wave's LDS accesses before it are done before those after it.
+AJ_DEV void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 AJ_DEV uint32_t key_tok(uint64_t k) { return (uint32_t)(k >> 32); }
 AJ_DEV uint32_t key_pos(uint64_t k) { return (uint32_t)k; }
 
@@ -178,10 +184,9 @@ __global__ __launch_bounds__(256) void sort_scatter_kernel(const int32_t *tok, c
       }
       const int below = __popcll(peers & ((1ull << lane) - 1));
       rank[q] = dig[q] >= 0 ? wcnt[w][dig[q]] + below : 0;
-      // every lane has read its count (one wave, in order) before a leader adds
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();   // every lane has read its count before a leader adds
       if (dig[q] >= 0 && below == 0) wcnt[w][dig[q]] += __popcll(peers);
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
     }
     __syncthreads();
 #pragma unroll
