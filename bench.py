@@ -483,9 +483,10 @@ def measure(cfg, steps, warmup, u_steps, u_warmup, torch, capi, actor, record=Fa
     return r, live
 
 
-KERNEL_NAMES = {"gemm_nt": "gemm_mfma_kernel<Cfg8, true, true>",
-                "gemm_nn": "gemm_mfma_kernel<Cfg8, true, false>",
-                "gemm_tn": "gemm_mfma_kernel<Cfg8, false, false>",
+# the shorter reductions' classes take either tile size (one per product)
+KERNEL_NAMES = {"gemm_nt": "gemm_mfma_kernel<Cfg8 | CfgS, true, true>",
+                "gemm_nn": "gemm_mfma_kernel<Cfg8 | CfgS, true, false>",
+                "gemm_tn": "gemm_mfma_kernel<Cfg8 | CfgS, false, false>",
                 "gemm4_nt": "gemm_mfma_kernel<Cfg4, true, true>",
                 "gemm4_nn": "gemm_mfma_kernel<Cfg4, true, false>",
                 "gemm4_tn": "gemm_mfma_kernel<Cfg4, false, false>", "attn_fwd": "attn_fwd_mfma_kernel",

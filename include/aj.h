@@ -495,11 +495,13 @@ int aj_adamw_step(int64_t n, float *param, const float *grad, float *m, float *v
  * keeps besides the error text) and meant for a single-threaded driver.
  *   AJ_KC_MERGE      one aj_merge_timelines / aj_merge_timelines_text / aj_flatten_timelines call
  *   AJ_KC_GEMM_*     the MFMA GEMM, by operand layout (NT: both K-major;
- *                    NN: B N-major; TN: A M-major and B N-major), reductions
- *                    shorter than 4096 and products with the SwiGLU backward
- *                    or the adapters' second segment (8-wave kernel, or the
- *                    4-wave one of small tiles)
- *   AJ_KC_GEMM4_*    the same layouts, longer reductions (4-wave kernels)
+ *                    NN: B N-major; TN: A M-major and B N-major): 256x256
+ *                    tiles of 8 waves, or 128x128 tiles where those fill the
+ *                    chip better; products with the SwiGLU backward or the
+ *                    adapters' second segment always.  With the adding up of
+ *                    a split reduction's pieces
+ *   AJ_KC_GEMM4_*    the same layouts, 256x256 tiles of 4 waves: reductions
+ *                    (or pieces of one) of 4096 and more that run in such tiles
  *   AJ_KC_ATTN_FWD / AJ_KC_ATTN_BWD   the attention kernels of one call
  *   AJ_KC_LM_FWD     the fused logits + log-sum-exp kernel of the LM head
  *   AJ_KC_LM_DZ      the fused logits-recompute + d logits kernel (one per chunk)

@@ -565,7 +565,7 @@ int gemm(const Gemm &g, hipStream_t s) {
   if (mfma) {
     const GemmPlan pl = gemm_plan(g.M, g.N, g.K, cap, g.K2 > 0 || g.swiglu_gu);
     int kc = g.a_kmajor ? (g.b_kmajor ? AJ_KC_GEMM_NT : AJ_KC_GEMM_NN) : AJ_KC_GEMM_TN;
-    if (g.K >= kLongK && g.K2 == 0 && !g.swiglu_gu) kc += AJ_KC_GEMM4_NT - AJ_KC_GEMM_NT;
+    if (pl.long_k) kc += AJ_KC_GEMM4_NT - AJ_KC_GEMM_NT;   // the kernel that runs
     const int tk =
         timing_begin(s, kc, g.recompute ? 0.0 : 2.0 * g.M * g.N * ((double)g.K + g.K2));
     if (g.a_kmajor && g.b_kmajor) launch_mfma<true, true>(g, ep, pl, s);

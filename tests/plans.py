@@ -1,0 +1,46 @@
+"""The library's dispatch rules and its products, called directly (ctypes on the
+C++ symbols that csrc/ops.h declares; test_plans.py checks the struct layouts)."""
+import ctypes as C
+
+from paper_2606_04484_amd import capi
+
+AJ_OK = 0
+vp, i32, i64, f32p = C.c_void_p, C.c_int, C.c_int64, C.c_void_p
+
+
+class GemmPlan(C.Structure):
+    _fields_ = [("tile", i32), ("long_k", C.c_bool), ("tiles", i32), ("whole", i32), ("split", i32),
+                ("k_piece", i32)]
+
+
+class Gemm(C.Structure):
+    _fields_ = [("M", i32), ("N", i32), ("K", i32), ("A", vp), ("lda", i64), ("a_kmajor", C.c_bool),
+                ("B", vp), ("ldb", i64), ("b_kmajor", C.c_bool), ("C", vp), ("ldc", i64),
+                ("c_f32", C.c_bool), ("out", i32), ("R", vp), ("partial", vp),
+                ("partial_cap", C.c_size_t), ("swiglu_gu", vp), ("recompute", C.c_bool), ("A2", vp),
+                ("lda2", i64), ("B2", vp), ("ldb2", i64), ("K2", i32)]
+
+
+STRUCTS = {"GemmPlan": GemmPlan, "Gemm": Gemm}
+
+
+def _fn(name, restype, *argtypes):
+    f = getattr(capi.lib(), name)
+    f.restype, f.argtypes = restype, list(argtypes)
+    return f
+
+
+def gemm_plan(M, N, K, cap, eight_wave=False):
+    return _fn("_ZN2aj9gemm_planEiiimb", GemmPlan, i32, i32, i32, C.c_size_t, C.c_bool)(
+        M, N, K, cap, eight_wave)
+
+
+def partial_floats(M, N):
+    """gemm_partial_floats: at most 512 blocks of 256 x 256, 16 a tile."""
+    return min(16 * -(-M // 256) * -(-N // 256), 512) * 65536
+
+
+def gemm_bf16(g, stream):
+    rc = _fn("_ZN2aj4gemmItEEiRKNS_4GemmEP12ihipStream_t", i32, C.POINTER(Gemm), vp)(
+        C.byref(g), stream)
+    assert rc == AJ_OK, rc

@@ -238,11 +238,11 @@ BF16_CASES = {
     # backward epilogue on its element-wise edge path) and the down
     # projection's reduction ends in a ragged 8-wide k-step
     "hd64_ff328": dict(hd=64, d=256, hq=4, hkv=2, ff=328, vocab=2000, chunk=768),
-    # reductions of 4096 and more on every 4-wave layout, each ending in a
-    # ragged 32-wide k-step: the down projection (NT, k = d_ff = 4104), the
-    # gate/up input gradient (NN, k = 2 d_ff = 8208), d h of the first vocab
-    # chunk (NN, k = 4104; the second chunk is 896 wide), and unmerged the
-    # weight gradients (TN, k = 5856 tokens); few output tiles, so split-K
+    # reductions of 4096 and more in every layout, each ending in a ragged
+    # 32-wide k-step: the down projection (NT, k = d_ff = 4104), the gate/up
+    # input gradient (NN, k = 2 d_ff = 8208), d h of the first vocab chunk (NN,
+    # k = 4104; the second chunk is 896 wide), and unmerged the weight gradients
+    # (TN, k = 5856 tokens); few output tiles, so in pieces
     "hd64_long_k": dict(hd=64, d=256, hq=4, hkv=2, ff=4104, vocab=5000, chunk=4104),
     # one query head per key/value head: the dK/dV pass walks a single head,
     # so its item count is often not a multiple of its three LDS stages
@@ -260,21 +260,25 @@ def test_bf16(name, merged):
 
 
 @pytest.mark.parametrize("merged", [True, False])
-def test_bf16_long_reductions_reach_the_4wave_kernels(merged):
-    """The long-reduction case at the bf16 bounds, with the launch record showing
-    that the 4-wave NN and NT kernels ran (and TN on the unmerged layout, whose
-    5856 tokens are the weight gradients' reduction).  The forward projections
-    read the [out][in] weights here, so that they run the NT layout (with the
-    transposed copies they run NN, as test_transposed_weights_bitwise_equal
-    checks)."""
+def test_bf16_long_reductions(merged):
+    """The long-reduction case at the bf16 bounds, with the plans of its long
+    products: few output tiles, so all of them in pieces shorter than 4096, and the
+    launch record counts none in the classes of the 4-wave 256x256 kernel (which
+    test_gpu_gemm_plans.py compares in every layout).  The forward projections read
+    the [out][in] weights here, so that they run the NT layout (with the transposed
+    copies they run NN, as test_transposed_weights_bitwise_equal checks)."""
+    from tests import plans
     m = bf16_case_model(**BF16_CASES["hd64_long_k"])
     case = Case(workload(m), noise_std=0.3, margin=0.05)
+    n = case.merged.n_tok if merged else case.unmerged.n_tok
+    for M, N, K in [(n, m.d_model, m.d_ff), (n, m.d_model, 2 * m.d_ff), (m.d_model, m.d_ff, n)]:
+        p = plans.gemm_plan(M, N, K, min(2000 * n, plans.partial_floats(M, N)))
+        assert p.split > 1 and not p.long_k
     got = run_gpu(case, merged, record=True, transposed_weights=False)
     rec = got["rec"]
     print("launches: " + ", ".join(f"{k} {v[1]}" for k, v in rec.items() if v[1]), flush=True)
-    assert rec["gemm4_nn"][1] > 0 and rec["gemm4_nt"][1] > 0
-    if not merged:
-        assert case.unmerged.n_tok >= 4096 and rec["gemm4_tn"][1] > 0
+    for k in ("nn", "nt", "tn"):
+        assert rec["gemm_" + k][1] > 0 and rec["gemm4_" + k][1] == 0
     check(case, got, merged, 2e-2, 1e-2, 1e-2, 0.999)
 
 
