@@ -526,11 +526,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_dq_mfma_kernel(AttnBwdArgs a,
     df[kk] = __builtin_bit_cast(bf16x8_t, y);
   }
   const float lse2 = qv ? a.lse[(int64_t)h * a.n_tok + q] : 0.f;       // log2 units
-  // the lane's query keeps one negated delta: every dP^T element starts from it
+  // the lane's query keeps one negated delta: every dP^T element starts from it.
+  // Eight waves keep it spread over 16 registers (48000 tokens in 40 segments, 28
+  // heads of 128: 877 us, 897 spread at each half); four, whose copies take more
+  // address registers, would spill then (895 us, 846 spread at each half), except
+  // at head_dim 64.
   const float ndlt = qv ? a.delta[(int64_t)h * a.n_tok + q] : 0.f;
+  constexpr bool kSpread = NW >= 8 || HD == 64;
   f32x16_t dp0;
+  auto spread = [&](float v) __attribute__((always_inline)) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) dp0[r] = ndlt;
+    for (int r = 0; r < 16; ++r) dp0[r] = v;
+  };
+  spread(ndlt);
   f32x16_t acc[DT];
 #pragma unroll
   for (int i = 0; i < DT; ++i)
@@ -553,6 +561,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_dq_mfma_kernel(AttnBwdArgs a,
   auto half = [&](const int tt, const int st, const int k0,
                   const bool full) __attribute__((always_inline)) {
     f32x16_t s, dp;   // S^T and dP^T - delta, set by rows_times_pair
+    if constexpr (!kSpread) {
+      float v = ndlt;
+      asm volatile("" : "+v"(v));   // a value the compiler does not keep spread
+      spread(v);
+    }
     rows_times_pair<HD>(s, dp, L, st * T, (2 + st) * T, 32 * tt, qf, df, dp0);
     if (full) {
 #pragma unroll
@@ -607,7 +620,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_dq_mfma_kernel(AttnBwdArgs a,
 // ------------------------------------------------------------------ dK, dV
 // One workgroup: 32 * NW keys of one key/value head (NW waves of 32), a lane
 // owns one key; it walks the query heads of the group (or of its part of them,
-// see dkv_parts) and the segment's query tiles of 64 after the keys (items),
+// see attn_dkv_parts) and the segment's query tiles of 64 after the keys (items),
 // staged three deep (Q, dO and the queries' LSE and delta) and shared by all
 // the waves.
 //
@@ -1067,12 +1080,17 @@ bool attn_mfma_supported(int hd, const void *p0, const void *p1, const void *p2)
 // heads (240 workgroups) 148.1 / 134.0, two of 1173 44.3 / 36.4, four of 2000
 // of 28 heads 160.5 / 152.8, 40 of 1200 685 / 635; the other side: two of 3573
 // of 12 heads (336) 117.7 / 125.1, four of 3625 193.6 / 211.0, one of 45769 of
-// 40 heads 20340 / 21986.  dQ alike.  Two waves were never faster than the
+// 40 heads 20340 / 21986.  dQ: one of 600 of 12 heads 24.4 / 22.4, of 5000 173.7
+// / 163.9, 20 of 1500 292 / 268, four of 2000 of 28 heads 199 / 200, 40 of 1200
+// 877 / 846, 24 of 2000 of 40 heads 1709 / 1726; the other side: two of 3573 of 12
+// heads 153.4 / 147.2, five of 3887 of 28 heads 798 / 830, six of 4000 of 40 heads
+// 1447 / 1496, one of 45769 25727 / 27609 (at head_dim 64 four waves are 3 to 10 %
+// faster there too, up to these lengths).  Two waves were never faster than the
 // better of these by more than 6 %, and up to 40 % slower.
 constexpr int kRowWaves = 8, kDkvWaves = 4;
-static bool few_rows(int n_tok, int n_seg, int heads) {
+int attn_row_waves(int n_tok, int n_seg, int heads) {
   const int64_t wgs = (int64_t)((n_tok + 32 * kRowWaves - 1) / (32 * kRowWaves)) * heads;
-  return wgs <= 256 || (int64_t)n_seg * 2048 >= n_tok;
+  return wgs <= 256 || (int64_t)n_seg * 2048 >= n_tok ? 4 : kRowWaves;
 }
 
 // In how many parts the dK/dV pass takes the query heads of a group.  Its
@@ -1092,7 +1110,7 @@ static bool few_rows(int n_tok, int n_seg, int heads) {
 // and where one part is taken, 1 / as many as the group has heads:
 //   40 heads, 8 KV: 8000 1298 / 1406; 6 of 4000 2158 / 2445; 28 heads: 40 of
 //   1200 1199 / 1702.
-static int dkv_parts(const AttnBwdArgs &a) {
+int attn_dkv_parts(const AttnBwdArgs &a) {
   if (!a.part || !aligned16(a.part)) return 1;
   const int group = a.Hq / a.Hkv;
   const int64_t keys = ((int64_t)a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves) * a.Hkv;
@@ -1118,7 +1136,7 @@ static void launch_fwd(const AttnArgs &a, hipStream_t s) {
     const int n_qt = (a.n_tok + 32 * NW - 1) / (32 * NW);
     attn_fwd_mfma_kernel<HD, NW><<<(unsigned)n_qt * a.Hq, 64 * NW, 0, s>>>(a, n_qt);
   };
-  if (few_rows(a.n_tok, a.n_seg, a.Hq)) go(Ci<4>{});
+  if (attn_row_waves(a.n_tok, a.n_seg, a.Hq) == 4) go(Ci<4>{});
   else go(Ci<kRowWaves>{});
 }
 
@@ -1137,9 +1155,9 @@ static void launch_bwd(const AttnBwdArgs &a, hipStream_t s) {
     const int n_qt = (a.n_tok + 32 * NW - 1) / (32 * NW);
     attn_dq_mfma_kernel<HD, NW><<<(unsigned)n_qt * a.Hq, 64 * NW, 0, s>>>(a, n_qt);
   };
-  if (few_rows(a.n_tok, a.n_seg, a.Hq)) dq(Ci<4>{});
+  if (attn_row_waves(a.n_tok, a.n_seg, a.Hq) == 4) dq(Ci<4>{});
   else dq(Ci<kRowWaves>{});
-  const int n_kt = (a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves), parts = dkv_parts(a);
+  const int n_kt = (a.n_tok + 32 * kDkvWaves - 1) / (32 * kDkvWaves), parts = attn_dkv_parts(a);
   attn_dkv_mfma_kernel<HD, kDkvWaves>
       <<<(unsigned)n_kt * a.Hkv * parts, 64 * kDkvWaves, 0, s>>>(a, parts);
   if (parts > 1) {

@@ -133,5 +133,9 @@ int attn_bwd(const AttnBwdArgs &a, hipStream_t s);
 bool attn_mfma_supported(int hd, const void *p0, const void *p1, const void *p2);
 int attn_fwd_mfma(const AttnArgs &a, hipStream_t s);
 int attn_bwd_mfma(const AttnBwdArgs &a, hipStream_t s);
+// its waves per workgroup in the forward and dQ passes, and the parts of a group's
+// query heads in the dK/dV pass
+int attn_row_waves(int n_tok, int n_seg, int heads);
+int attn_dkv_parts(const AttnBwdArgs &a);
 
 }  // namespace aj

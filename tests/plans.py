@@ -5,7 +5,7 @@ import ctypes as C
 from paper_2606_04484_amd import capi
 
 AJ_OK = 0
-vp, i32, i64, f32p = C.c_void_p, C.c_int, C.c_int64, C.c_void_p
+vp, i32, i64 = C.c_void_p, C.c_int, C.c_int64
 
 
 class GemmPlan(C.Structure):
@@ -21,7 +21,18 @@ class Gemm(C.Structure):
                 ("lda2", i64), ("B2", vp), ("ldb2", i64), ("K2", i32)]
 
 
-STRUCTS = {"GemmPlan": GemmPlan, "Gemm": Gemm}
+class AttnArgs(C.Structure):
+    _fields_ = [("n_tok", i32), ("n_seg", i32), ("Hq", i32), ("Hkv", i32), ("hd", i32), ("base", i32),
+                ("cu_seqlens", vp), ("qkv", vp), ("o", vp), ("lse", vp), ("scale", C.c_float)]
+
+
+class AttnBwdArgs(C.Structure):
+    _fields_ = [("n_tok", i32), ("n_seg", i32), ("Hq", i32), ("Hkv", i32), ("hd", i32), ("base", i32),
+                ("cu_seqlens", vp), ("qkv", vp), ("o", vp), ("dout", vp), ("lse", vp), ("delta", vp),
+                ("dqkv", vp), ("scale", C.c_float), ("part", vp), ("part_floats", C.c_size_t)]
+
+
+STRUCTS = {"GemmPlan": GemmPlan, "Gemm": Gemm, "AttnArgs": AttnArgs, "AttnBwdArgs": AttnBwdArgs}
 
 
 def _fn(name, restype, *argtypes):
@@ -43,4 +54,24 @@ def partial_floats(M, N):
 def gemm_bf16(g, stream):
     rc = _fn("_ZN2aj4gemmItEEiRKNS_4GemmEP12ihipStream_t", i32, C.POINTER(Gemm), vp)(
         C.byref(g), stream)
+    assert rc == AJ_OK, rc
+
+
+def attn_row_waves(n_tok, n_seg, heads):
+    return _fn("_ZN2aj14attn_row_wavesEiii", i32, i32, i32, i32)(n_tok, n_seg, heads)
+
+
+def attn_dkv_parts(a):
+    return _fn("_ZN2aj14attn_dkv_partsERKNS_11AttnBwdArgsE", i32, C.POINTER(AttnBwdArgs))(C.byref(a))
+
+
+def attn_fwd_bf16(a, stream):
+    rc = _fn("_ZN2aj8attn_fwdItEEiRKNS_8AttnArgsEP12ihipStream_t", i32, C.POINTER(AttnArgs), vp)(
+        C.byref(a), stream)
+    assert rc == AJ_OK, rc
+
+
+def attn_bwd_bf16(a, stream):
+    rc = _fn("_ZN2aj8attn_bwdItEEiRKNS_11AttnBwdArgsEP12ihipStream_t", i32, C.POINTER(AttnBwdArgs), vp)(
+        C.byref(a), stream)
     assert rc == AJ_OK, rc
