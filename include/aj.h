@@ -271,9 +271,12 @@ typedef struct {
   const int32_t *pos;           /* [n_tok] position of each token inside its segment (RoPE) */
 } aj_varlen;
 
-/* Bytes of the activation arena the forward fills and the backward reads. */
+/* Bytes of the activation arena the forward fills and the backward reads,
+ * scratch of the forward's split reductions included: 8 KB per token, at most
+ * 67 MB (float32: 17 MB). */
 size_t aj_block_saved_bytes(const aj_block_cfg *cfg, int32_t n_tok);
-/* Scratch for either direction. */
+/* Scratch for either direction; up to 134 MB of it (float32: 17 MB) is for split
+ * reductions. */
 size_t aj_block_workspace_bytes(const aj_block_cfg *cfg, int32_t n_tok, int32_t n_seg);
 /* x, y: [n_tok, d] in cfg->dtype.  `saved` (aj_block_saved_bytes) receives
  * the activations the backward reads and must outlive it; ws: at least
@@ -347,6 +350,8 @@ typedef struct {                /* float32, accumulated */
 } aj_lora_grads;
 
 size_t aj_lora_saved_bytes(const aj_block_cfg *cfg, int32_t rank, int32_t n_tok);
+/* aj_block_workspace_bytes and the adapters' own, up to 134 MB of it (float32: 17
+ * MB) for their split reductions. */
 size_t aj_lora_workspace_bytes(const aj_block_cfg *cfg, int32_t rank, int32_t n_tok);
 int aj_stack_lora_fwd(const aj_block_cfg *cfg, int32_t n_layers, const aj_block_weights *w,
                       const aj_lora *lora, const aj_varlen *vl, const void *x, void *y,
@@ -415,6 +420,7 @@ typedef struct {
 } aj_loss_in;
 
 size_t aj_loss_saved_bytes(const aj_loss_cfg *cfg, int32_t n_tgt);
+/* Up to 134 MB of it (float32: 17 MB) is for split reductions. */
 size_t aj_loss_workspace_bytes(const aj_loss_cfg *cfg, int32_t n_tgt);
 /* h [n_tok, d], final_norm [d], w_vocab [vocab, d] in cfg->dtype.
  * logprob, lse: [n_tgt] float32 (written).  stats: float32[5] accumulated:

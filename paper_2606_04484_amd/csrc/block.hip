@@ -19,9 +19,13 @@ struct Saved {
   size_t bytes;
 };
 
-// That scratch: enough for 256 pieces of 256 x 256 from 8389 tokens on, and 8 KB
-// per token (a few percent of the arena) below, where tiles are fewer as well.
-size_t fwd_part_floats(int64_t n) { return std::min<int64_t>(2000 * n, 256 * 65536); }
+// That scratch: 8 KB per token, up to 256 pieces of 256 x 256 (67 MB, from 8389
+// tokens on) for bfloat16 and 1024 of 64 x 64 (17 MB) for float32.  Of the whole
+// arena at 2000 tokens: a tenth for a 1.5B-class block, 5 % for a 7B-class one, 4 %
+// for a 32B-class one, 45 % for the float32 workload's (33 % at its 3443 tokens).
+size_t fwd_part_floats(int64_t n, bool f32) {
+  return std::min<int64_t>(2000 * n, f32 ? 1024 * 4096 : 256 * 65536);
+}
 
 Saved carve_saved(const aj_block_cfg &c, int n, void *base) {
   const size_t es = c.dtype == AJ_BF16 ? 2 : 4;
@@ -39,7 +43,7 @@ Saved carve_saved(const aj_block_cfg &c, int n, void *base) {
   s.rstd1 = cv.take<float>(n);
   s.lse = cv.take<float>((int64_t)c.n_q_heads * n);
   s.rstd2 = cv.take<float>(n);
-  s.part_floats = fwd_part_floats(n);
+  s.part_floats = fwd_part_floats(n, c.dtype != AJ_BF16);
   s.part = cv.take<float>(s.part_floats);
   s.bytes = cv.bytes();
   return s;
@@ -71,8 +75,9 @@ BwdWs carve_bwd(const aj_block_cfg &c, int n, void *base) {
   w.dg_part = cv.take<float>(aj::rmsnorm_bwd_part_floats(n, (int)d));
   // sums of split reductions: the weight gradients (2F x d the largest) and the
   // products of n rows (2F columns the widest)
-  w.splitk_floats = std::max(aj::gemm_partial_floats(2 * F, std::max(d, q)),
-                             aj::gemm_partial_floats(n, 2 * F));
+  const bool f32 = c.dtype != AJ_BF16;
+  w.splitk_floats = std::max(aj::gemm_partial_floats(2 * F, std::max(d, q), f32),
+                             aj::gemm_partial_floats(n, 2 * F, f32));
   w.splitk = cv.take<float>(w.splitk_floats);
   w.bytes = cv.bytes();
   return w;
@@ -134,8 +139,9 @@ size_t carve_lora_bwd(const aj_block_cfg &c, int r, int n, void *base, LoraBwd *
   aj::Carver cv(base);
   float *v32 = cv.take<float>((int64_t)n * r);
   void *vs = cv.take<char>((int64_t)n * r * es);
-  const size_t sk = std::max(aj::gemm_partial_floats(r, std::max(2 * c.d_ff, proj_out(c, kQkv))),
-                             aj::gemm_partial_floats(n, r));
+  const bool f32 = c.dtype != AJ_BF16;
+  const size_t sk = std::max(aj::gemm_partial_floats(r, std::max(2 * c.d_ff, proj_out(c, kQkv)), f32),
+                             aj::gemm_partial_floats(n, r, f32));
   float *part = cv.take<float>(sk);
   if (lb) { lb->v32 = v32; lb->vs = vs; lb->partial = part; lb->partial_floats = sk; }
   return cv.bytes();

@@ -533,6 +533,15 @@ GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool eight_wave) {
   return best;
 }
 
+int gemm_f32_pieces(int M, int N, int K, size_t partial_cap) {
+  const int tiles = ((M + kFTile - 1) / kFTile) * ((N + kFTile - 1) / kFTile);
+  int S = 1;
+  while (S < kMaxSplit && S < K / (2 * kFBK) && tiles * S < 512 &&
+         (size_t)tiles * (S + 1) * (kFTile * kFTile) <= partial_cap)
+    ++S;
+  return S;
+}
+
 template <typename T>
 int gemm(const Gemm &g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return AJ_OK;
@@ -575,14 +584,8 @@ int gemm(const Gemm &g, hipStream_t s) {
     timing_end(s, tk);
     return check_launch("gemm");
   }
-  // 64 x 64 tiles, in pieces while the chip has CUs to spare and a piece two
-  // k-steps
   const int tiles = ((g.M + kFTile - 1) / kFTile) * ((g.N + kFTile - 1) / kFTile);
-  int S = 1;
-  if (g.K2 == 0)
-    while (S < gemm_split_k(g.M, g.N, g.K) && tiles * S < 512 &&
-           (size_t)tiles * (S + 1) * (kFTile * kFTile) <= cap)
-      ++S;
+  const int S = g.K2 == 0 ? gemm_f32_pieces(g.M, g.N, g.K, cap) : 1;
   const int k_piece = ((g.K > 0 ? g.K : 0) + S - 1) / S;
   const Pieces pc{S > 1 ? 0 : tiles, S > 1 ? tiles : 0, S, (k_piece + kFBK - 1) / kFBK * kFBK,
                   g.partial};

@@ -43,20 +43,17 @@ int chunk_group(const aj_loss_cfg &c) {
   return c.dtype == AJ_BF16 && c.vocab_chunk <= 16384 ? 2 : 1;
 }
 
-// Widths of the groups: full groups, and the last one (narrower when the
-// vocab is not a multiple of the group's width).
-void group_widths(const aj_loss_cfg &c, int64_t *full, int64_t *last) {
+// Width of the groups (the last one is narrower when the vocab is not a multiple).
+int64_t group_width(const aj_loss_cfg &c) {
   const int64_t cw = c.vocab_chunk < c.vocab ? c.vocab_chunk : c.vocab;
   const int64_t gw = cw * chunk_group(c);
-  *full = gw < c.vocab ? gw : c.vocab;
-  *last = c.vocab % *full == 0 ? *full : c.vocab % *full;
+  return gw < c.vocab ? gw : c.vocab;
 }
 
 LossWs carve_ws(const aj_loss_cfg &c, int n_tgt, void *base) {
   const size_t es = c.dtype == AJ_BF16 ? 2 : 4;
   const int64_t cw = c.vocab_chunk < c.vocab ? c.vocab_chunk : c.vocab;
-  int64_t gfull, glast;
-  group_widths(c, &gfull, &glast);
+  const int64_t gfull = group_width(c);
   aj::Carver cv(base);
   LossWs w;
   w.z = cv.take<float>(c.dtype == AJ_BF16 ? 1 : (int64_t)n_tgt * cw);
@@ -71,8 +68,9 @@ LossWs carve_ws(const aj_loss_cfg &c, int n_tgt, void *base) {
   w.part = cv.take<float>(kFinBlocks * 8);
   w.dhn = cv.take<float>((int64_t)n_tgt * c.d_model);
   w.dg_part = cv.take<float>(aj::rmsnorm_bwd_part_floats(n_tgt, c.d_model));
-  w.splitk_floats = std::max(aj::gemm_partial_floats(gfull, c.d_model),
-                             aj::gemm_partial_floats(n_tgt, c.d_model));
+  const bool f32 = c.dtype != AJ_BF16;
+  w.splitk_floats = std::max(aj::gemm_partial_floats(gfull, c.d_model, f32),
+                             aj::gemm_partial_floats(n_tgt, c.d_model, f32));
   w.splitk = cv.take<float>(w.splitk_floats);
   w.bytes = cv.bytes();
   return w;

@@ -83,22 +83,20 @@ struct GemmPlan {
 GemmPlan gemm_plan(int M, int N, int K, size_t partial_cap, bool eight_wave);
 
 constexpr int kMaxSplit = 16;
-// Scratch for the products of M x N outputs, in floats: every split stays
-// inside min(kMaxSplit * tiles, 512) blocks of 256 x 256.  Not a function of
-// the reduction, and never less for a larger M or N: a caller's buffers sized
-// for its largest pack serve the smaller ones.
-inline size_t gemm_partial_floats(int64_t M, int64_t N) {
-  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  return (size_t)(tiles * kMaxSplit < 512 ? tiles * kMaxSplit : 512) * 65536;
+// Scratch for the products of M x N outputs, in floats.  bfloat16: every split
+// stays inside min(kMaxSplit * tiles, 512) blocks of 256 x 256 (134 MB at most);
+// float32: no more than min(kMaxSplit * tiles, 1024) of the 64 x 64 blocks its
+// products run in (17 MB), as many as gemm_f32_pieces ever asks for.  Not a
+// function of the reduction, and never less for a larger M or N: a caller's
+// buffers sized for its largest pack serve the smaller ones.
+inline size_t gemm_partial_floats(int64_t M, int64_t N, bool f32) {
+  const int64_t t = f32 ? 64 : 256, most = f32 ? 1024 : 512;
+  const int64_t tiles = ((M + t - 1) / t) * ((N + t - 1) / t);
+  return (size_t)((tiles * kMaxSplit < most ? tiles * kMaxSplit : most) * t * t);
 }
-// The most pieces of a reduction over K whose sums of a whole M x N output fit
-// that scratch, no piece shorter than 64.
-inline int gemm_split_k(int M, int N, int K) {
-  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  int S = kMaxSplit < 512 / tiles ? kMaxSplit : 512 / tiles;
-  if (S > K / 64) S = K / 64;
-  return S < 1 ? 1 : S;
-}
+// Pieces of a reduction over K on the 64 x 64 tiles: enough for 512 workgroups, no
+// piece shorter than two k-steps.
+int gemm_f32_pieces(int M, int N, int K, size_t partial_cap);
 
 // ---------------------------------------------------------------- attention
 struct AttnArgs {

@@ -1,9 +1,9 @@
-"""Split-K workspace sizing against the dispatch heuristic (CPU only): builds
+"""Scratch of split reductions against the plans that use it (CPU only): builds
 tests/native/splitk_sizing.cpp, which includes the library's loss and block
 sources and calls their own workspace carving, and runs it on the host
-(nothing is launched).  Regression: the LM head's weight-gradient product
+(nothing is launched).  Regressions: the LM head's weight-gradient product
 once split its last, narrower vocab chunk into a workspace carved for the
-full chunks only."""
+full chunks only; float32 calls once reserved eight times what they could use."""
 import os
 import subprocess
 
