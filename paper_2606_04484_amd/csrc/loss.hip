@@ -324,8 +324,9 @@ __global__ __launch_bounds__(Cfg::NT, 1) void lm_fwd_fused_kernel(
   // each: reduce in the lane, then across the four with two exchanges.
   const int col0 = n0 + gemm_core::acc_col<Cfg>(wn, 0, lane);   // columns col0 + 16 j + r
   if (zkeep) {
-    // the tile's logits for the backward, four consecutive columns at a time
-    const bool vec = V % 4 == 0;
+    // the tile's logits for the backward, four consecutive columns at a time where
+    // their rows are aligned
+    const bool vec = V % 4 == 0 && ((uintptr_t)zkeep & 15) == 0;
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i) {
       const int m = m0 + gemm_core::acc_row<Cfg>(wm, i, lane);
