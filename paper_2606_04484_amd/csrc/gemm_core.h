@@ -6,15 +6,18 @@
 // K-major one as [row][k], an M/N-major one as [k][row], whose MFMA fragments
 // come out of LDS already transposed through ds_read_b64_tr_b16.
 //
-// Why 16x16x32 and not 32x32x16: these products run at the chip's power limit,
+// Why 16x16x32 and not 32x32x16: these products run at the chip's power limit
+// (the clock falls below 1.8 GHz while they run, and from registers alone random
+// operands reach 1880 TFLOP/s where constant ones reach 2480, csrc/ceiling.hip),
 // and the smaller tile's accumulator traffic per product is half (a quarter of
-// the accumulators, half the products).  From registers with random operands,
-// 256 accumulators per lane: 2041 TFLOP/s against 1788.  With it went the
-// fragment reads' address arithmetic (one address per operand, constants for
-// the rest) and the copies' (buffer resources in scalar registers): the loop
-// holds MFMAs, LDS reads, copies and scalar instructions only.  32B-class LM
-// head over 18897 targets 104.3 -> 89.9 ms, 32B block over one 45769-token
-// segment 197.1 -> 183.9 ms, 7B block over 19437 tokens 30.2 -> 27.3 ms.
+// the accumulators, half the products).  That file's loop with 256 accumulators
+// per lane and random operands: 2041 TFLOP/s with this instruction, 1788 with the
+// larger one.  With it went the fragment reads' address arithmetic (one address
+// per operand, constants for the rest) and the copies' (buffer resources in
+// scalar registers): the loop holds MFMAs, LDS reads, copies and scalar
+// instructions only.  32B-class LM head over 18897 targets 104.3 -> 89.9 ms, 32B
+// block over one 45769-token segment 197.1 -> 183.9 ms, 7B block over 19437
+// tokens 30.2 -> 27.3 ms.
 #pragma once
 #include <utility>
 #include "common.h"

@@ -99,9 +99,9 @@ def gpu_run(case):
 
 def test_long_reduction_layouts_ran(gpu_run):
     """The step as the actor runs it: the forward projections read the
-    transposed weight copies, so every long reduction runs the 4-wave NN or TN
-    layout (the NT one is compared with the oracle at small shapes, with the
-    [out][in] weights)."""
+    transposed weight copies, so its long reductions run the NN or TN layout,
+    those in whole 256x256 tiles or long pieces on the 4-wave kernel (the NT one
+    is compared in test_gpu_gemm_plans.py)."""
     rec = gpu_run["rec"]
     for k in ("gemm4_nn", "gemm4_tn", "lm_fwd", "lm_dz", "attn_fwd", "attn_bwd"):
         assert rec[k][1] > 0, k

@@ -15,6 +15,8 @@ import numpy as np
 import pytest
 import torch
 
+from tests import plans
+
 pytestmark = pytest.mark.gpu
 
 # (targets, d, vocab, chunk): reductions below one k-step, of 1 to 9 steps (so
@@ -22,9 +24,12 @@ pytestmark = pytest.mark.gpu
 SIZES = [(1, 8, 8, 8), (31, 24, 40, 40), (33, 40, 264, 96), (255, 64, 256, 256), (257, 104, 520, 264),
          (300, 136, 1000, 512), (64, 160, 96, 96), (129, 264, 288, 144), (700, 32, 2056, 2056),
          (96, 520, 130, 128),
-         # reductions in pieces: every tile's (few tiles), and those of the tiles
-         # past a full round of 256 (65 x 5 tiles of d hidden)
+         # reductions in pieces (PIECES): every tile's (few tiles), and those of the
+         # tiles past a full round of 256 (65 x 5 tiles of d hidden)
          (300, 136, 4104, 4104), (2000, 264, 2600, 2600), (16500, 1032, 2056, 2056)]
+# of these the plans of d hidden and of dW: (tile, whole tiles, pieces of the rest)
+PIECES = {(300, 4104): ((128, 0, 15), (128, 66, 1)), (2000, 2600): ((128, 0, 5), (128, 0, 4)),
+          (16500, 2056): ((256, 256, 3), (256, 0, 5))}
 
 
 def _bf(x):
@@ -38,6 +43,10 @@ def test_lm_head_products(n, d, vocab, chunk, transposed):
     if transposed and vocab % 8:
         pytest.skip("the transposed copy needs vocab % 8 == 0")
     print(f"lm head n={n} d={d} vocab={vocab} chunk={chunk} transposed={transposed}", flush=True)
+    if (n, vocab) in PIECES:
+        cap = max(plans.partial_floats(chunk, d), plans.partial_floats(n, d))
+        p = [plans.gemm_plan(n, d, chunk, cap), plans.gemm_plan(chunk, d, n, cap)]
+        assert tuple((x.tile, x.whole, x.split) for x in p) == PIECES[n, vocab]
     rng = np.random.default_rng(n * 7 + d)
     h = _bf(rng.standard_normal((n + 1, d)))
     gain = _bf(1 + 0.1 * rng.standard_normal(d))
@@ -124,12 +133,15 @@ def test_second_segment_in_pieces():
     m = dataclasses.replace(bf16_case_model(hd=64, d=256, hq=4, hkv=2, ff=4104), n_layers=1)
     case = Case(workload(m, n_traj=2), noise_std=0.3, margin=0.05,
                 lora=make_lora_numpy(m, 40, seed=2001, b_std=0.05), lora_scale=0.5)
+    n = case.merged.n_tok
+    assert plans.gemm_plan(n, m.d_model, m.d_ff, min(2000 * n, 256 * 65536), True).split > 1
     check(case, run_gpu(case, True), True, 2e-2, 1e-2, 1e-2, 0.999)
 
 
-@pytest.mark.parametrize("hq,hkv,hd,ff", [(7, 1, 64, 128), (7, 1, 64, 512), (7, 1, 64, 1024),
-                                          (6, 2, 128, 1536), (4, 4, 128, 512)])
-def test_key_gradients_in_parts(hq, hkv, hd, ff):
+@pytest.mark.parametrize("hq,hkv,hd,ff,parts", [(7, 1, 64, 128, 1), (7, 1, 64, 512, 4),
+                                                (7, 1, 64, 1024, 7), (6, 2, 128, 1536, 3),
+                                                (4, 4, 128, 512, 1)])
+def test_key_gradients_in_parts(hq, hkv, hd, ff, parts):
     """The dK/dV pass with a group's query heads in one part (128 and the group
     of one head), in uneven ones (512: the scratch holds 4 parts of 7 heads) and
     one head each: against the oracle at the same bounds."""
@@ -138,4 +150,8 @@ def test_key_gradients_in_parts(hq, hkv, hd, ff):
     print(f"dK/dV parts hq={hq} hkv={hkv} hd={hd} ff={ff}", flush=True)
     m = bf16_case_model(hd=hd, d=256, hq=hq, hkv=hkv, ff=ff)
     case = Case(workload(m, n_traj=2), noise_std=0.3, margin=0.05)
+    # the backward's scratch is d gate and d up: n rows of ff floats
+    n, n_seg = case.merged.n_tok, case.merged.n_seg
+    b = plans.AttnBwdArgs(n_tok=n, n_seg=n_seg, Hq=hq, Hkv=hkv, hd=hd, part=256, part_floats=n * ff)
+    assert plans.attn_dkv_parts(b) == parts
     check(case, run_gpu(case, True), True, 2e-2, 1e-2, 1e-2, 0.999)
