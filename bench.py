@@ -72,12 +72,14 @@ def log(msg):
 # and a step launches the class `launches` times (the same mix of products),
 # otherwise the line reports null.
 TRAFFIC = {
-    ("gemm4_tn", "block1.5b-64x8"): {"bytes_per_launch": 4840.4e6, "launches": 27,
-                                     "sources": "c74b4918568820ba"},
-    ("gemm4_tn", "long32b-8x60"): {"bytes_per_launch": 17968.3e6, "launches": 56,
-                                   "sources": "c74b4918568820ba"},
-    ("gemm4_nn", "long32b-8x60"): {"bytes_per_launch": 23618.3e6, "launches": 68,
-                                   "sources": "c74b4918568820ba"},
+    ("gemm4_nn", "long32b-8x60"): {"bytes_per_launch": 22575.0e6, "launches": 68,
+                                   "sources": "6b1a5c469d87077a"},
+    ("gemm4_tn", "long32b-8x60"): {"bytes_per_launch": 40604.6e6, "launches": 56,
+                                   "sources": "6b1a5c469d87077a"},
+    ("gemm4_nn", "block1.5b-64x8"): {"bytes_per_launch": 5090.0e6, "launches": 21,
+                                     "sources": "6b1a5c469d87077a"},
+    ("gemm4_tn", "block1.5b-64x8"): {"bytes_per_launch": 6448.3e6, "launches": 27,
+                                     "sources": "6b1a5c469d87077a"},
 }
 
 

@@ -110,8 +110,10 @@ AJ_DEV int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >
 // by asynchronous direct-to-LDS global loads: a wave instruction moves a block
 // of 64 x 16 bytes, lane l's 16 bytes landing at block + 16*l, so the layout
 // inside a block is chosen through each lane's global address.  Both layouts
-// let a fragment read hit all 64 banks with addresses that differ between the
-// wave's fragments by a constant only:
+// spread the 16 lanes l..l+15 of a fragment read over all 64 banks, with
+// addresses that differ between the wave's fragments by a constant only.  The
+// counters see no conflict on M/N-major operands; K-major ones still conflict,
+// a third of the cycles the LDS is busy in a product with one of each:
 //   K-major operand (rows r, k contiguous): [R][32], 16 rows a block, the
 //     16-byte chunk c of row r at r*64 + 16*(c ^ ((r >> 2) & 3))  (ds_read_b128)
 //   M/N-major operand (k rows, r contiguous): whole k rows, 512 / R of them a
