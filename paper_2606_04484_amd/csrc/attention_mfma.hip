@@ -527,9 +527,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_dq_mfma_kernel(AttnBwdArgs a,
   }
   const float lse2 = qv ? a.lse[(int64_t)h * a.n_tok + q] : 0.f;       // log2 units
   // the lane's query keeps one negated delta: every dP^T element starts from it.
-  // Eight waves keep it spread over 16 registers (48000 tokens in 40 segments, 28
-  // heads of 128: 877 us, 897 spread at each half); four, whose copies take more
-  // address registers, would spill then (895 us, 846 spread at each half), except
+  // Eight waves keep it spread over 16 registers (48000 tokens in 40 segments of
+  // 28 heads of 128: 856 us, 871 spread at each half); four, whose copies take more
+  // address registers, would spill then (831 us, 805 spread at each half), except
   // at head_dim 64.
   const float ndlt = qv ? a.delta[(int64_t)h * a.n_tok + q] : 0.f;
   constexpr bool kSpread = NW >= 8 || HD == 64;
@@ -1080,13 +1080,14 @@ bool attn_mfma_supported(int hd, const void *p0, const void *p1, const void *p2)
 // heads (240 workgroups) 148.1 / 134.0, two of 1173 44.3 / 36.4, four of 2000
 // of 28 heads 160.5 / 152.8, 40 of 1200 685 / 635; the other side: two of 3573
 // of 12 heads (336) 117.7 / 125.1, four of 3625 193.6 / 211.0, one of 45769 of
-// 40 heads 20340 / 21986.  dQ: one of 600 of 12 heads 24.4 / 22.4, of 5000 173.7
-// / 163.9, 20 of 1500 292 / 268, four of 2000 of 28 heads 199 / 200, 40 of 1200
-// 877 / 846, 24 of 2000 of 40 heads 1709 / 1726; the other side: two of 3573 of 12
-// heads 153.4 / 147.2, five of 3887 of 28 heads 798 / 830, six of 4000 of 40 heads
-// 1447 / 1496, one of 45769 25727 / 27609 (at head_dim 64 four waves are 3 to 10 %
-// faster there too, up to these lengths).  Two waves were never faster than the
-// better of these by more than 6 %, and up to 40 % slower.
+// 40 heads 20340 / 21986.  dQ: one of 5000 of 12 heads 187 / 169, two of 1173 50.8
+// / 41.5, four of 2000 of 28 heads 197 / 190, 40 of 1200 856 / 805; the other side:
+// two of 3573 of 12 heads 142 / 151, four of 3625 248 / 261, six of 4000 of 40
+// heads 1370 / 1399, one of 45769 25727 / 27609.  Uneven lengths move the crossing
+// by a few percent either way (7147 of 12 heads in 3303 and 3844: forward 125 /
+// 119, dQ 153 / 147), as does head_dim 64 (four waves 3 to 10 % faster on the other
+// side too, up to 20000 tokens).  Two waves were never faster than the better of
+// these by more than 6 %, and up to 40 % slower.
 constexpr int kRowWaves = 8, kDkvWaves = 4;
 int attn_row_waves(int n_tok, int n_seg, int heads) {
   const int64_t wgs = (int64_t)((n_tok + 32 * kRowWaves - 1) / (32 * kRowWaves)) * heads;
