@@ -284,7 +284,10 @@ size_t aj_block_workspace_bytes(const aj_block_cfg *cfg, int32_t n_tok, int32_t 
  * pointer, AJ_ERR_SHAPE for sizes or offsets out of range or query heads
  * that do not group evenly over the key/value heads, AJ_ERR_UNSUPPORTED for
  * a head_dim outside 8..128 (multiple of 8) or another dtype,
- * AJ_ERR_WORKSPACE for a short workspace. */
+ * AJ_ERR_WORKSPACE for a short workspace.
+ * Infinities and NaN in a row reach the rows that attend to it; with bfloat16
+ * and head_dim 64 or 128 also other rows within the same tiles (64 keys, up to
+ * 256 queries), whose masked weights are zeros in the same matrix products. */
 int aj_varlen_block_fwd(const aj_block_cfg *cfg, const aj_block_weights *w, const aj_varlen *vl,
                         const void *x, void *y, void *saved, void *ws, size_t ws_bytes,
                         void *stream);
